@@ -26,7 +26,6 @@ namespace {
 constexpr int NIN = 16;   // (N+1)^2 features of a degree-3 quadrilateral
 constexpr int HID = 64;
 constexpr long NPAR = (long)HID * NIN + HID + (long)HID * HID + HID + HID + 1;
-constexpr int SB = 32;    // samples per workgroup of the gradient kernel
 
 __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 __device__ __forceinline__ uint16_t f2bf(float f)
@@ -52,146 +51,469 @@ __device__ __forceinline__ MlpView mlp_view(const uint16_t *th)
     return v;
 }
 
-// z of one sample; the weights are read at lane-uniform addresses (scalar loads)
-__device__ __forceinline__ float mlp_z(const MlpView &w, const float *x)
+// ---------------------------------------------------------------- the network on the matrix cores
+// Every layer is formed transposed, Y^T = W X^T, for 16 samples at a time:
+// the BF16 weights are the exact A operand, and every FP32 activation enters
+// the B operand as the sum of three BF16 parts (x = hi + mid + lo to within
+// 2^-26 |x|), so each product is exact in FP32 and the result is the FP32
+// network up to the summation order.  The first layer (16 inputs) uses
+// v_mfma_f32_16x16x16_bf16, operand layout (lane l, i = 0..3):
+// A[l % 16][4 (l / 16) + i], B[4 (l / 16) + i][l % 16],
+// D[4 (l / 16) + i][l % 16]; a layer's D is therefore already a B operand of
+// the next layer.  The 64-wide layers use the K = 32 form
+// v_mfma_f32_16x16x32_bf16 on two 16-row D blocks at a time: a lane's eight
+// B values are its four rows of each block, and its eight A values are the
+// weights of the same hidden units (whatever hidden unit an operand slot
+// carries, A and B carry the same one, so the sum runs over the block pair).
+typedef short mx_s4 __attribute__((ext_vector_type(4)));
+typedef float mx_f4 __attribute__((ext_vector_type(4)));
+typedef __bf16 mx_b8 __attribute__((ext_vector_type(8)));
+typedef short mx_s8 __attribute__((ext_vector_type(8)));
+
+// x = hi + mid + lo in BF16 (round to nearest even: the hardware conversion).
+// An infinite x is its own hi part with mid = lo = 0, so that it acts as it
+// would in FP32 arithmetic.
+__device__ __forceinline__ void split3(float x, short &h, short &m, short &l)
 {
-    float h1[HID];
+    const __bf16 bh = (__bf16)x;
+    const float fh = (float)bh;
+    const float r1 = x == fh ? 0.f : x - fh;
+    const __bf16 bm = (__bf16)r1;
+    const float r2 = r1 - (float)bm;
+    h = __builtin_bit_cast(short, bh);
+    m = __builtin_bit_cast(short, bm);
+    l = __builtin_bit_cast(short, (__bf16)r2);
+}
+template <class V>
+__device__ __forceinline__ void split3v(const float *x, int n, V &h, V &m, V &l)
+{
 #pragma unroll
-    for (int j = 0; j < HID; ++j) {
-        float a = bf2f(w.b1[j]);
-#pragma unroll
-        for (int c = 0; c < NIN; ++c) a = fmaf(bf2f(w.W1[j * NIN + c]), x[c], a);
-        h1[j] = a > 0.f ? a : 0.f;
+    for (int i = 0; i < n; ++i) {
+        short a, b, c;
+        split3(x[i], a, b, c);
+        h[i] = a;
+        m[i] = b;
+        l[i] = c;
     }
-    float z = bf2f(w.b3[0]);
-    for (int k = 0; k < HID; ++k) {
-        float a = bf2f(w.b2[k]);
-#pragma unroll
-        for (int j = 0; j < HID; ++j) a = fmaf(bf2f(w.W2[k * HID + j]), h1[j], a);
-        z = fmaf(bf2f(w.W3[k]), a > 0.f ? a : 0.f, z);
-    }
-    return z;
 }
 
+// two 4-value operands of the K = 16 form as one 8-value operand of the
+// K = 32 form, reinterpreted as a whole vector (built element by element
+// from bit-cast BF16 values, the operand reached the instruction wrongly
+// packed with this compiler, although its bits read back unchanged)
+__device__ __forceinline__ mx_b8 as_b8(const mx_s8 &t) { return __builtin_bit_cast(mx_b8, t); }
+__device__ __forceinline__ mx_b8 join8(const mx_s4 &p, const mx_s4 &q)
+{
+    return as_b8(__builtin_shufflevector(p, q, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// acc + a (bh + bm + bl), the small parts first
+__device__ __forceinline__ mx_f4 mfma3(const mx_s4 &a, const mx_s4 &bh, const mx_s4 &bm, const mx_s4 &bl, mx_f4 acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bl, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bm, acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bh, acc, 0, 0, 0);
+}
+__device__ __forceinline__ mx_f4 mfma3k32(const mx_b8 &a, const mx_b8 &bh, const mx_b8 &bm, const mx_b8 &bl, mx_f4 acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bl, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bm, acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bh, acc, 0, 0, 0);
+}
+// acc + (ah + am + al)(bh + bm + bl) without the three products below 2^-26
+__device__ __forceinline__ mx_f4 mfma6k32(const mx_b8 *a, const mx_b8 *b, mx_f4 acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[2], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2], b[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[0], acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0], acc, 0, 0, 0);
+}
+
+constexpr int MX_TILE = 16;
+constexpr unsigned MLP_GRID = 2 * 256;   // workgroups of the inference kernels: two wavefronts per SIMD of 256 CUs
+static_assert(NIN == 16 && HID == 64, "the tiling below is written for 16 inputs and 64 hidden units");
+
+// The weights a lane holds (col = lane % 16, kq = lane / 16): the A blocks of
+// W1 (hidden 16 b + col, inputs 4 kq + i) and W2 (out 16 c + col, hidden units
+// of the block pair), and the biases and W3 of the hidden units 16 b + 4 kq + i
+// it holds in D.  They stay in registers while a wavefront walks its tiles.
+struct MlpRegs {
+    mx_s4 A1[4];
+    mx_b8 A2[4][2];
+    float B1[4][4], B2[4][4], W3[4][4], b3;
+};
+__device__ __forceinline__ void mlp_load(const MlpView &w, int col, int kq, MlpRegs &r)
+{
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        mx_s4 q[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            r.A1[b][i] = (short)w.W1[(16 * b + col) * NIN + 4 * kq + i];
+            r.B1[b][i] = bf2f(w.b1[16 * b + 4 * kq + i]);
+            r.B2[b][i] = bf2f(w.b2[16 * b + 4 * kq + i]);
+            r.W3[b][i] = bf2f(w.W3[16 * b + 4 * kq + i]);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) q[c][i] = (short)w.W2[(16 * b + col) * HID + 16 * c + 4 * kq + i];
+        }
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) r.A2[b][kb] = join8(q[2 * kb], q[2 * kb + 1]);
+    }
+    r.b3 = bf2f(w.b3[0]);
+}
+
+// The network on the 16 samples of a tile: x = the lane's four inputs
+// 4 kq + i of sample col.  Returns z (in all four lanes of the sample); h1
+// and a2 receive the first layer's outputs and the second layer's sums of the
+// lane's hidden units 16 b + 4 kq + i.  The biases start the accumulators.
+__device__ __forceinline__ float mlp_tile(const MlpRegs &w, const float *x, float (&h1)[4][4], float (&a2)[4][4])
+{
+    mx_s4 xh, xm, xl;
+    split3v(x, 4, xh, xm, xl);
+    mx_s4 hh[4], hm[4], hl[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        mx_f4 acc = {w.B1[b][0], w.B1[b][1], w.B1[b][2], w.B1[b][3]};
+        acc = mfma3(w.A1[b], xh, xm, xl, acc);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) h1[b][i] = acc[i] > 0.f ? acc[i] : 0.f;
+        split3v(h1[b], 4, hh[b], hm[b], hl[b]);
+    }
+    mx_b8 kh[2], km[2], kl[2];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+        kh[kb] = join8(hh[2 * kb], hh[2 * kb + 1]);
+        km[kb] = join8(hm[2 * kb], hm[2 * kb + 1]);
+        kl[kb] = join8(hl[2 * kb], hl[2 * kb + 1]);
+    }
+    float z = 0.f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        mx_f4 acc = {w.B2[c][0], w.B2[c][1], w.B2[c][2], w.B2[c][3]};
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) acc = mfma3k32(w.A2[c][kb], kh[kb], km[kb], kl[kb], acc);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            a2[c][i] = acc[i];
+            z = fmaf(w.W3[c][i], acc[i] > 0.f ? acc[i] : 0.f, z);
+        }
+    }
+    z += __shfl_xor(z, 16);
+    z += __shfl_xor(z, 32);
+    return z + w.b3;
+}
+
+// Inference of many samples, bit for bit the FP32 network with its sums taken
+// in index order: v_mfma_f32_16x16x4_f32 adds its four products to the
+// accumulator one after the other, each rounded as an FP32 fused
+// multiply-add, so a chain of them is the chain of scalar ones.  A wavefront
+// takes 64 samples in four groups of 16; operand layout (lane l, kq = l / 16):
+// A[l % 16][kq], B[kq][l % 16], D[4 kq + i][l % 16].  Row r of a D block is
+// made hidden unit 16 b + 4 (r % 4) + r / 4 (by the A row it is given), so that
+// register i of D is the B operand of units 16 b + 4 i + kq, in index order.
+// The output layer, one sum per sample, is formed by one lane per sample from
+// the second layer's outputs in LDS (rows of 80: the four rows a store
+// touches lie on different banks).
+// Bound by the matrix cores' FP32 rate: 80 instructions of 32 cycles per 16
+// samples are 85 us for 1 310 720 samples on 1024 SIMDs at 2.4 GHz.  Measured
+// there: 151 us (161 without loading the next group ahead), against 405 us
+// for one lane per sample on the vector units with scalar weight loads.  The
+// three-part BF16 split of the indicator's tile takes 84 us but rounds
+// differently, and these outputs are FP32 sums that callers compare.
+constexpr int FW = 64, FROW = FW + 16;
 __global__ void __launch_bounds__(256) k_mlp_forward(const uint16_t *theta, const float *x, long n, float alpha_max,
                                                      float *z_out, double *alpha_out)
 {
-    const long s = (long)blockIdx.x * 256 + threadIdx.x;
-    if (s >= n) return;
+    __shared__ float pool[4][HID * FROW];
+    const int lane = threadIdx.x & 63;
+    const int col = lane & 15, kq = lane >> 4;
+    const long wave = ((long)blockIdx.x * 256 + threadIdx.x) >> 6;
+    const long nwaves = ((long)gridDim.x * 256) >> 6;
+    const long ntiles = (n + FW - 1) / FW;
+    if (wave >= ntiles) return;                       // uniform per wavefront
     const MlpView w = mlp_view(theta);
-    float xs[NIN];
+    float *h2 = pool[threadIdx.x >> 6];
+    float A1[4][4], A2[4][16], B1[4][4], B2[4][4];
 #pragma unroll
-    for (int c = 0; c < NIN; ++c) xs[c] = x[s * NIN + c];
-    const float z = mlp_z(w, xs);
-    if (z_out) z_out[s] = z;
-    if (alpha_out) alpha_out[s] = (double)alpha_max / (1.0 + exp(-(double)z));
+    for (int b = 0; b < 4; ++b) {
+        const int row = 16 * b + 4 * (col & 3) + (col >> 2);   // hidden unit of the lane's A row
+#pragma unroll
+        for (int t = 0; t < 4; ++t) A1[b][t] = bf2f(w.W1[row * NIN + 4 * t + kq]);
+#pragma unroll
+        for (int t = 0; t < 16; ++t) A2[b][t] = bf2f(w.W2[row * HID + 4 * t + kq]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            B1[b][i] = bf2f(w.b1[16 * b + 4 * i + kq]);
+            B2[b][i] = bf2f(w.b2[16 * b + 4 * i + kq]);
+        }
+    }
+    // the lane's inputs of the group of 16 samples that starts at s0 (the
+    // next group's are loaded ahead: a group's products hide one round trip)
+    float nx[4];
+    auto load = [&](long s0) {
+        const bool sv = s0 + col < n;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) nx[t] = sv ? x[(s0 + col) * NIN + 4 * t + kq] : 0.f;
+    };
+    load(wave * FW);
+    for (long tile = wave; tile < ntiles; tile += nwaves) {
+        for (int g = 0; g < 4; ++g) {
+            float xs[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) xs[t] = nx[t];
+            load(g < 3 ? tile * FW + 16 * (g + 1) : (tile + nwaves) * FW);
+            mx_f4 a1[4], a2[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                a1[b] = mx_f4{B1[b][0], B1[b][1], B1[b][2], B1[b][3]};
+                a2[b] = mx_f4{B2[b][0], B2[b][1], B2[b][2], B2[b][3]};
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) a1[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(A1[b][t], xs[t], a1[b], 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                const float h = a1[t >> 2][t & 3] > 0.f ? a1[t >> 2][t & 3] : 0.f;   // unit 4 t + kq
+#pragma unroll
+                for (int b = 0; b < 4; ++b) a2[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(A2[b][t], h, a2[b], 0, 0, 0);
+            }
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    h2[(16 * b + 4 * i + kq) * FROW + 16 * g + col] = a2[b][i] > 0.f ? a2[b][i] : 0.f;
+        }
+        element_sync<64>();
+        const long s = tile * FW + lane;
+        float z = bf2f(w.b3[0]);
+#pragma unroll
+        for (int k = 0; k < HID; ++k) z = fmaf(bf2f(w.W3[k]), h2[k * FROW + lane], z);
+        if (s < n) {
+            if (z_out) z_out[s] = z;
+            if (alpha_out) alpha_out[s] = (double)alpha_max / (1.0 + exp(-(double)z));
+        }
+        element_sync<64>();      // before the next tile overwrites the rows
+    }
 }
 
-// Gradient of the mean binary cross-entropy of sigmoid(z) against y over
-// n_total samples: one workgroup per SB samples writes its partial gradient.
-__global__ void __launch_bounds__(256) k_mlp_grad(const uint16_t *theta, const float *x, const float *y, long n,
-                                                  long n_total, float *partial, float *partial_loss)
+// Gradient of the mean binary cross-entropy of sigmoid(z) against y over n
+// samples.  A wavefront takes 32 samples at a time: two forward tiles, the
+// back-propagated sums D1^T = W2^T D2^T on the matrix cores as the forward
+// layers, and the weight gradients gW2 = D2 H1^T, gW1 = D1 X^T as products
+// with the samples as the contraction (K = 32).  There a lane needs eight
+// samples of one hidden unit where the layers leave four hidden units of one
+// sample, so H1, D2, D1 and X pass through LDS (FP32 rows of GROW values:
+// 16-byte aligned reads, rows four apart on different banks).  Both operands
+// are split in three BF16 parts, six products each.  The weight gradients
+// stay in accumulators over all of a wavefront's samples; the four wavefronts
+// of a workgroup add theirs through LDS and write one partial gradient.
+// Bound by latency at the usual batch (8192 samples are one pass of 256
+// wavefronts): loss, gradient and Adam step of a batch 88 -> 23 us against
+// vector arithmetic fed from LDS with 32 samples per workgroup (24 us) and a
+// reduction that walked its 256 partials one after the other on 21
+// workgroups (63 us).  Relative error of the gradient against 64 bits at
+// 8192 samples as before, 3e-7.
+constexpr int GS = 32;             // samples per wavefront and pass
+constexpr int GROW = GS + 4;       // LDS row
+constexpr int GROWS = 3 * HID + NIN;   // H1, D2, D1, X
+constexpr int GWAVES = 4;
+constexpr int GBLOCKS = 256;       // most workgroups (one per CU)
+static_assert(GROWS * GROW >= NPAR, "a wavefront's gradient fits its LDS rows");
+
+// eight samples (8 kq ..) of LDS row r as the three BF16 parts of an operand
+__device__ __forceinline__ void grad_operand(const float *rows, int r, int kq, mx_b8 *o)
 {
-    __shared__ float xs[SB][NIN];
-    __shared__ float A1[SB][HID], A2[SB][HID], D1[SB][HID], D2[SB][HID];
-    __shared__ float dz[SB], ls[SB];
-    const int tid = threadIdx.x;
-    const long s0 = (long)blockIdx.x * SB;
-    const MlpView w = mlp_view(theta);
-    for (int i = tid; i < SB * NIN; i += 256) {
-        const int s = i / NIN, c = i - s * NIN;
-        xs[s][c] = (s0 + s < n) ? x[(s0 + s) * NIN + c] : 0.f;
-    }
-    __syncthreads();
-    for (int i = tid; i < SB * HID; i += 256) {
-        const int s = i / HID, j = i - s * HID;
-        float a = bf2f(w.b1[j]);
+    float v[8];
 #pragma unroll
-        for (int c = 0; c < NIN; ++c) a = fmaf(bf2f(w.W1[j * NIN + c]), xs[s][c], a);
-        A1[s][j] = a;
-    }
-    __syncthreads();
-    for (int i = tid; i < SB * HID; i += 256) {
-        const int s = i / HID, k = i - s * HID;
-        float a = bf2f(w.b2[k]);
-        for (int j = 0; j < HID; ++j) a = fmaf(bf2f(w.W2[k * HID + j]), fmaxf(A1[s][j], 0.f), a);
-        A2[s][k] = a;
-    }
-    __syncthreads();
-    if (tid < SB) {
-        const int s = tid;
-        float z = bf2f(w.b3[0]);
-        for (int k = 0; k < HID; ++k) z = fmaf(bf2f(w.W3[k]), fmaxf(A2[s][k], 0.f), z);
-        const bool in = s0 + s < n;
-        const float yy = in ? y[s0 + s] : 0.f;
-        const float sg = 1.f / (1.f + expf(-z));
-        dz[s] = in ? (sg - yy) / (float)n_total : 0.f;
-        // BCE with logits, stable form: log(1 + e^z) - y z
-        ls[s] = in ? ((z > 0.f ? z + log1pf(expf(-z)) : log1pf(expf(z))) - yy * z) : 0.f;
-    }
-    __syncthreads();
-    for (int i = tid; i < SB * HID; i += 256) {
-        const int s = i / HID, k = i - s * HID;
-        D2[s][k] = A2[s][k] > 0.f ? dz[s] * bf2f(w.W3[k]) : 0.f;
-    }
-    __syncthreads();
-    for (int i = tid; i < SB * HID; i += 256) {
-        const int s = i / HID, j = i - s * HID;
-        float a = 0.f;
-        for (int k = 0; k < HID; ++k) a = fmaf(bf2f(w.W2[k * HID + j]), D2[s][k], a);
-        D1[s][j] = A1[s][j] > 0.f ? a : 0.f;
-    }
-    __syncthreads();
-    float *g = partial + (long)blockIdx.x * NPAR;
-    float *gW1 = g, *gb1 = gW1 + HID * NIN, *gW2 = gb1 + HID, *gb2 = gW2 + HID * HID, *gW3 = gb2 + HID, *gb3 = gW3 + HID;
-    for (int i = tid; i < HID * NIN; i += 256) {
-        const int j = i / NIN, c = i - j * NIN;
-        float a = 0.f;
-        for (int s = 0; s < SB; ++s) a = fmaf(D1[s][j], xs[s][c], a);
-        gW1[i] = a;
-    }
-    for (int i = tid; i < HID * HID; i += 256) {
-        const int k = i / HID, j = i - k * HID;
-        float a = 0.f;
-        for (int s = 0; s < SB; ++s) a = fmaf(D2[s][k], fmaxf(A1[s][j], 0.f), a);
-        gW2[i] = a;
-    }
-    if (tid < HID) {
-        float a1 = 0.f, a2 = 0.f, a3 = 0.f;
-        for (int s = 0; s < SB; ++s) {
-            a1 += D1[s][tid];
-            a2 += D2[s][tid];
-            a3 = fmaf(dz[s], fmaxf(A2[s][tid], 0.f), a3);
+    for (int i = 0; i < 8; ++i) v[i] = rows[r * GROW + 8 * kq + i];
+    mx_s8 h, m, l;
+    split3v(v, 8, h, m, l);
+    o[0] = as_b8(h);
+    o[1] = as_b8(m);
+    o[2] = as_b8(l);
+}
+
+__global__ void __launch_bounds__(64 * GWAVES) k_mlp_grad(const uint16_t *theta, const float *x, const float *y, long n,
+                                                          float *partial, float *partial_loss)
+{
+    __shared__ __align__(16) float pool[GWAVES][GROWS * GROW];
+    __shared__ float lsum[GWAVES];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int col = lane & 15, kq = lane >> 4;
+    const MlpView w = mlp_view(theta);
+    MlpRegs r;
+    mlp_load(w, col, kq, r);
+    mx_b8 A2T[4][2];               // W2 transposed: out j = 16 b + col, hidden units k of the block pair
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            mx_s8 q;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                q[i] = (short)w.W2[(16 * (2 * kb + (i >> 2)) + 4 * kq + (i & 3)) * HID + 16 * b + col];
+            A2T[b][kb] = as_b8(q);
         }
-        gb1[tid] = a1;
-        gb2[tid] = a2;
-        gW3[tid] = a3;
+    float *H1 = pool[wv], *D2 = H1 + HID * GROW, *D1 = D2 + HID * GROW, *X = D1 + HID * GROW;
+    mx_f4 gW2[4][4], gW1[4];
+    float gb1[4][4], gb2[4][4], gW3[4][4], gb3 = 0.f, loss = 0.f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        gW1[c] = mx_f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            gW2[c][b] = mx_f4{0.f, 0.f, 0.f, 0.f};
+            gb1[c][b] = gb2[c][b] = gW3[c][b] = 0.f;
+        }
+    }
+    const float inv_n = 1.f / (float)n;
+    const long chunks = (n + GS - 1) / GS;
+    for (long ch = (long)blockIdx.x * GWAVES + wv; ch < chunks; ch += (long)gridDim.x * GWAVES) {
+        for (int t = 0; t < GS / MX_TILE; ++t) {
+            const int sl = MX_TILE * t + col;          // sample within the pass
+            const long s = ch * GS + sl;
+            const bool in = s < n;
+            float xs[4], h1[4][4], a2[4][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) xs[i] = in ? x[s * NIN + 4 * kq + i] : 0.f;
+            const float yy = in ? y[s] : 0.f;
+            const float z = mlp_tile(r, xs, h1, a2);
+            const float sg = 1.f / (1.f + expf(-z));
+            const float dz = in ? (sg - yy) * inv_n : 0.f;
+            if (kq == 0 && in) {
+                // BCE with logits, stable form: log(1 + e^z) - y z
+                loss += (z > 0.f ? z + log1pf(expf(-z)) : log1pf(expf(z))) - yy * z;
+                gb3 += dz;
+            }
+            mx_s4 dh[4], dm[4], dl[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float d2[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int row = 16 * c + 4 * kq + i;
+                    d2[i] = a2[c][i] > 0.f ? dz * r.W3[c][i] : 0.f;
+                    gb2[c][i] += d2[i];
+                    gW3[c][i] = fmaf(dz, a2[c][i] > 0.f ? a2[c][i] : 0.f, gW3[c][i]);
+                    D2[row * GROW + sl] = d2[i];
+                    H1[row * GROW + sl] = h1[c][i];
+                }
+                split3v(d2, 4, dh[c], dm[c], dl[c]);
+            }
+            mx_b8 kh[2], km[2], kl[2];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                kh[kb] = join8(dh[2 * kb], dh[2 * kb + 1]);
+                km[kb] = join8(dm[2 * kb], dm[2 * kb + 1]);
+                kl[kb] = join8(dl[2 * kb], dl[2 * kb + 1]);
+            }
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                mx_f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) acc = mfma3k32(A2T[b][kb], kh[kb], km[kb], kl[kb], acc);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float d1 = h1[b][i] > 0.f ? acc[i] : 0.f;
+                    gb1[b][i] += d1;
+                    D1[(16 * b + 4 * kq + i) * GROW + sl] = d1;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) X[(4 * kq + i) * GROW + sl] = xs[i];
+        }
+        element_sync<64>();
+        mx_b8 a[4][3], o[3];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) grad_operand(D2, 16 * c + col, kq, a[c]);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            grad_operand(H1, 16 * b + col, kq, o);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) gW2[c][b] = mfma6k32(a[c], o, gW2[c][b]);
+        }
+        grad_operand(X, col, kq, o);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            mx_b8 d[3];
+            grad_operand(D1, 16 * b + col, kq, d);
+            gW1[b] = mfma6k32(d, o, gW1[b]);
+        }
+        element_sync<64>();      // before the next pass overwrites the rows
+    }
+    // the sums over samples of the per-unit gradients: over the 16 columns
+    auto column_sum = [](float v) {
+#pragma unroll
+        for (int m = 1; m < 16; m <<= 1) v += __shfl_xor(v, m);
+        return v;
+    };
+    loss = column_sum(loss);
+    gb3 = column_sum(gb3);
+    float *g = pool[wv];          // this wavefront's own rows
+    float *oW1 = g, *ob1 = oW1 + HID * NIN, *oW2 = ob1 + HID, *ob2 = oW2 + HID * HID, *oW3 = ob2 + HID, *ob3 = oW3 + HID;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = 16 * c + 4 * kq + i;
+            oW1[row * NIN + col] = gW1[c][i];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) oW2[row * HID + 16 * b + col] = gW2[c][b][i];
+            const float s1 = column_sum(gb1[c][i]), s2 = column_sum(gb2[c][i]), s3 = column_sum(gW3[c][i]);
+            if (col == 0) {
+                ob1[row] = s1;
+                ob2[row] = s2;
+                oW3[row] = s3;
+            }
+        }
+    if (lane == 0) {
+        ob3[0] = gb3;
+        lsum[wv] = loss;
+    }
+    __syncthreads();
+    for (int p = tid; p < NPAR; p += 64 * GWAVES) {
+        float s = pool[0][p];
+#pragma unroll
+        for (int k = 1; k < GWAVES; ++k) s += pool[k][p];
+        partial[(long)blockIdx.x * NPAR + p] = s;
     }
     if (tid == 0) {
-        float a = 0.f, l = 0.f;
-        for (int s = 0; s < SB; ++s) {
-            a += dz[s];
-            l += ls[s];
-        }
-        gb3[0] = a;
-        partial_loss[blockIdx.x] = l;
+        float s = lsum[0];
+#pragma unroll
+        for (int k = 1; k < GWAVES; ++k) s += lsum[k];
+        partial_loss[blockIdx.x] = s;
     }
 }
 
-// sum of the partials in workgroup order (deterministic)
+// Sum of the workgroups' partial gradients in a fixed order.  A workgroup
+// takes RCOL consecutive parameters, 256 / RCOL lanes each: every lane adds
+// every (256 / RCOL)-th partial (loads in flight together), then a tree.
+constexpr int RCOL = 16, RSEG = 256 / RCOL;
 __global__ void __launch_bounds__(256) k_mlp_reduce(const float *partial, const float *partial_loss, int nblocks,
                                                     long n_total, float *grad, float *loss)
 {
-    const long p = (long)blockIdx.x * 256 + threadIdx.x;
-    if (p < NPAR) {
-        float a = 0.f;
-        for (int b = 0; b < nblocks; ++b) a += partial[(long)b * NPAR + p];
-        grad[p] = a;
-    } else if (p == NPAR && loss) {
-        float l = 0.f;
-        for (int b = 0; b < nblocks; ++b) l += partial_loss[b];
-        *loss = l / (float)n_total;
+    __shared__ float red[RSEG][RCOL];
+    const int c = threadIdx.x % RCOL, g = threadIdx.x / RCOL;
+    const long p = (long)blockIdx.x * RCOL + c;
+    const float *src = p < NPAR ? partial + p : partial_loss;
+    const long stride = p < NPAR ? NPAR : 1;
+    float a = 0.f;
+    if (p <= NPAR) {
+#pragma unroll 4
+        for (int b = g; b < nblocks; b += RSEG) a += src[(long)b * stride];
     }
+    red[g][c] = a;
+    __syncthreads();
+    for (int m = RSEG / 2; m > 0; m >>= 1) {
+        if (g < m) red[g][c] += red[g + m][c];
+        __syncthreads();
+    }
+    if (g > 0) return;
+    if (p < NPAR) grad[p] = red[0][c];
+    else if (p == NPAR && loss) *loss = red[0][c] / (float)n_total;
 }
 
 __global__ void __launch_bounds__(256) k_adam(long count, float *theta, float *m, float *v, const float *g, float lr,
@@ -219,69 +541,6 @@ __global__ void __launch_bounds__(256) k_to_bf16(long count, const float *x, uin
 // the training range [lo, hi] and a finite output; elsewhere the modal
 // coefficient already in alpha_raw stays.  alpha < alpha_min is cut to 0 as
 // for the modal indicator.
-// Inference for the blending coefficient on the matrix cores.  One
-// wavefront takes tiles of 16 elements and forms each layer transposed,
-// Y^T = W X^T: the BF16 weights are the exact A operand, and every FP32
-// activation enters the B operand as the sum of three BF16 parts
-// (x = hi + mid + lo to within 2^-24 |x|), so each product is exact in FP32
-// and the result is the FP32 network up to the summation order.  The first
-// layer (16 inputs) uses v_mfma_f32_16x16x16_bf16, operand layout (lane l,
-// i = 0..3): A[l % 16][4 (l / 16) + i], B[4 (l / 16) + i][l % 16],
-// D[4 (l / 16) + i][l % 16]; a layer's D is therefore already a B operand of
-// the next layer.  The second layer (64 hidden inputs) uses the K = 32 form
-// v_mfma_f32_16x16x32_bf16 on two 16-row D blocks at a time: a lane's eight
-// B values are its four rows of each block, and its eight A values are the
-// weights of the same hidden units (whatever hidden unit an operand slot
-// carries, A and B carry the same one, so the sum runs over the block pair).
-// The weights stay in registers while the wavefront walks its tiles.
-typedef short mx_s4 __attribute__((ext_vector_type(4)));
-typedef float mx_f4 __attribute__((ext_vector_type(4)));
-
-// x = hi + mid + lo in BF16 (round to nearest even: the hardware conversion)
-__device__ __forceinline__ void split3(const float *x, mx_s4 &h, mx_s4 &m, mx_s4 &l)
-{
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const __bf16 bh = (__bf16)x[i];
-        const float r1 = x[i] - (float)bh;
-        const __bf16 bm = (__bf16)r1;
-        const float r2 = r1 - (float)bm;
-        h[i] = __builtin_bit_cast(short, bh);
-        m[i] = __builtin_bit_cast(short, bm);
-        l[i] = __builtin_bit_cast(short, (__bf16)r2);
-    }
-}
-
-__device__ __forceinline__ mx_f4 mfma3(const mx_s4 &a, const mx_s4 &bh, const mx_s4 &bm, const mx_s4 &bl, mx_f4 acc)
-{
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bl, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bm, acc, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bh, acc, 0, 0, 0);
-}
-
-typedef __bf16 mx_b8 __attribute__((ext_vector_type(8)));
-typedef short mx_s8 __attribute__((ext_vector_type(8)));
-
-// two 4-value operands of the K = 16 form as one 8-value operand of the
-// K = 32 form, reinterpreted as a whole vector (built element by element
-// from bit-cast BF16 values, the operand reached the instruction wrongly
-// packed with this compiler, although its bits read back unchanged)
-__device__ __forceinline__ mx_b8 join8(const mx_s4 &p, const mx_s4 &q)
-{
-    const mx_s8 t = __builtin_shufflevector(p, q, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(mx_b8, t);
-}
-
-__device__ __forceinline__ mx_f4 mfma3k32(const mx_b8 &a, const mx_b8 &bh, const mx_b8 &bm, const mx_b8 &bl, mx_f4 acc)
-{
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bl, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bm, acc, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bh, acc, 0, 0, 0);
-}
-
-constexpr int MX_TILE = 16;
-static_assert(NIN == 16 && HID == 64, "the tiling below is written for 16 inputs and 64 hidden units");
-
 __global__ void __launch_bounds__(256) k_mlp_alpha(const uint16_t *theta, const float *features, const float *lo,
                                                    const float *hi, long nelem, double alpha_max, double alpha_min,
                                                    double *alpha_raw, const crk::Tables t, int epb, int *tiles)
@@ -292,32 +551,8 @@ __global__ void __launch_bounds__(256) k_mlp_alpha(const uint16_t *theta, const 
     const long nwaves = ((long)gridDim.x * 256) >> 6;
     const long ntiles = (nelem + MX_TILE - 1) / MX_TILE;
     if (wave >= ntiles) return;                       // uniform per wavefront
-    const MlpView w = mlp_view(theta);
-    // per-lane weights: A blocks of W1 (hidden 16b + col, inputs 4kq..) and
-    // W2 (out 16c + col, in 16b + 4kq ..), biases and W3 of the hidden units
-    // 16b + 4kq + i this lane holds in D
-    mx_s4 A1[4], A2[4][4];
-    float B1[4][4], B2[4][4], W3[4][4];
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            A1[b][i] = (short)w.W1[(16 * b + col) * NIN + 4 * kq + i];
-            B1[b][i] = bf2f(w.b1[16 * b + 4 * kq + i]);
-            B2[b][i] = bf2f(w.b2[16 * b + 4 * kq + i]);
-            W3[b][i] = bf2f(w.W3[16 * b + 4 * kq + i]);
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) A2[c][b][i] = (short)w.W2[(16 * c + col) * HID + 16 * b + 4 * kq + i];
-    }
-    mx_b8 A2k[4][2];
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) A2k[c][kb] = join8(A2[c][2 * kb], A2[c][2 * kb + 1]);
-    const float b3 = bf2f(w.b3[0]);
+    MlpRegs w;
+    mlp_load(mlp_view(theta), col, kq, w);
     float flo[4], fhi[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) { flo[i] = lo[4 * kq + i]; fhi[i] = hi[4 * kq + i]; }
@@ -325,7 +560,7 @@ __global__ void __launch_bounds__(256) k_mlp_alpha(const uint16_t *theta, const 
     for (long tile = wave; tile < ntiles; tile += nwaves) {
         const long e = tile * MX_TILE + col;
         const bool ev = e < nelem;
-        float x[4];
+        float x[4], h1[4][4], a2[4][4];
         bool inside = true;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -334,47 +569,7 @@ __global__ void __launch_bounds__(256) k_mlp_alpha(const uint16_t *theta, const 
         }
         // the four lanes of an element (col, col + 16, col + 32, col + 48)
         inside = inside && __shfl_xor((int)inside, 16) && __shfl_xor((int)inside, 32);
-        mx_s4 xh, xm, xl;
-        split3(x, xh, xm, xl);
-        // layer 1: H1^T block b = W1[16b.., :] X^T
-        float h1[4][4];
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            mx_f4 acc = {0.f, 0.f, 0.f, 0.f};
-            acc = mfma3(A1[b], xh, xm, xl, acc);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float v = acc[i] + B1[b][i];
-                h1[b][i] = v > 0.f ? v : 0.f;
-            }
-        }
-        mx_s4 hh[4], hm[4], hl[4];
-#pragma unroll
-        for (int b = 0; b < 4; ++b) split3(h1[b], hh[b], hm[b], hl[b]);
-        // layer 2 (K = 32: hidden blocks 2 kb and 2 kb + 1 together) and the
-        // output layer's partial dot product
-        mx_b8 kh[2], km[2], kl[2];
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            kh[kb] = join8(hh[2 * kb], hh[2 * kb + 1]);
-            km[kb] = join8(hm[2 * kb], hm[2 * kb + 1]);
-            kl[kb] = join8(hl[2 * kb], hl[2 * kb + 1]);
-        }
-        float z = 0.f;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            mx_f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) acc = mfma3k32(A2k[c][kb], kh[kb], km[kb], kl[kb], acc);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float v = acc[i] + B2[c][i];
-                z = fmaf(W3[c][i], v > 0.f ? v : 0.f, z);
-            }
-        }
-        z += __shfl_xor(z, 16);
-        z += __shfl_xor(z, 32);
-        z += b3;
+        const float z = mlp_tile(w, x, h1, a2);
         if (kq == 0 && ev && inside && isfinite(z)) {
             double a = alpha_max / (1.0 + exp(-(double)z));
             if (a < alpha_min) a = 0.0;
@@ -473,7 +668,7 @@ hipError_t launch_mlp_alpha(const uint16_t *theta, const float *features, const 
     // most two wavefronts per SIMD of the 256 CUs (the register budget)
     const long tiles = (nelem + MX_TILE - 1) / MX_TILE;
     long g = (tiles + 3) / 4;
-    if (g > 256 * 2) g = 256 * 2;
+    if (g > (long)MLP_GRID) g = MLP_GRID;
     // flags: local-phase tile flags of the 2D mesh described by *t, or nullptr
     const bool mark = flags != nullptr && t != nullptr;
     const Tables tt = mark ? *t : Tables{};
@@ -518,7 +713,10 @@ crk_status crk_mlp_forward(int nin, int hidden, const uint16_t *theta_bf16, cons
     if (st) return st;
     if (!theta_bf16 || !x || n < 0) { set_error(CRK_ERR_ARG, "null argument"); return CRK_ERR_ARG; }
     if (n == 0) return CRK_OK;
-    hipLaunchKernelGGL(k_mlp_forward, dim3(blocks(n, 256)), dim3(256), 0, (hipStream_t)stream, theta_bf16, x, (long)n,
+    // four wavefronts per workgroup, each walking tiles of 64 samples
+    unsigned g = blocks(n, 4 * FW);
+    if (g > MLP_GRID) g = MLP_GRID;
+    hipLaunchKernelGGL(k_mlp_forward, dim3(g), dim3(256), 0, (hipStream_t)stream, theta_bf16, x, (long)n,
                        (float)alpha_max, z, alpha);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? CRK_OK : hip_err(e, "crk_mlp_forward");
@@ -529,7 +727,7 @@ crk_status crk_mlp_grad_workspace_bytes(int nin, int hidden, int64_t n, size_t *
     crk_status st = check_shape(nin, hidden);
     if (st) return st;
     if (!bytes || n < 0) { set_error(CRK_ERR_ARG, "bad argument"); return CRK_ERR_ARG; }
-    const long nb = (long)blocks(n, SB);
+    const long nb = (long)blocks(n, GS);   // at least one partial gradient per workgroup
     *bytes = ((size_t)nb * NPAR * sizeof(float) + 255) / 256 * 256 + (size_t)nb * sizeof(float);
     return CRK_OK;
 }
@@ -543,12 +741,14 @@ crk_status crk_mlp_loss_grad(int nin, int hidden, const uint16_t *theta_bf16, co
     size_t need = 0;
     crk_mlp_grad_workspace_bytes(nin, hidden, n, &need);
     if (ws_bytes < need) { set_error(CRK_ERR_ARG, "workspace too small"); return CRK_ERR_ARG; }
-    const unsigned nb = blocks(n, SB);
+    // 128 samples per workgroup and pass, at most one workgroup per CU
+    unsigned nb = blocks(n, GS * GWAVES);
+    if (nb > GBLOCKS) nb = GBLOCKS;
     float *part = (float *)workspace;
     float *pl = (float *)((char *)workspace + ((size_t)nb * NPAR * sizeof(float) + 255) / 256 * 256);
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_mlp_grad, dim3(nb), dim3(256), 0, s, theta_bf16, x, y, (long)n, (long)n, part, pl);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3(blocks(NPAR + 1, 256)), dim3(256), 0, s, (const float *)part,
+    hipLaunchKernelGGL(k_mlp_grad, dim3(nb), dim3(64 * GWAVES), 0, s, theta_bf16, x, y, (long)n, part, pl);
+    hipLaunchKernelGGL(k_mlp_reduce, dim3(blocks(NPAR + 1, RCOL)), dim3(256), 0, s, (const float *)part,
                        (const float *)pl, (int)nb, (long)n, grad, loss);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? CRK_OK : hip_err(e, "crk_mlp_loss_grad");
