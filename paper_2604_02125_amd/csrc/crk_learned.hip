@@ -165,21 +165,23 @@ __device__ __forceinline__ void mlp_load(const MlpView &w, int col, int kq, MlpR
 }
 
 // The network on the 16 samples of a tile: x = the lane's four inputs
-// 4 kq + i of sample col.  Returns z (in all four lanes of the sample); h1
-// and a2 receive the first layer's outputs and the second layer's sums of the
-// lane's hidden units 16 b + 4 kq + i.  The biases start the accumulators.
-__device__ __forceinline__ float mlp_tile(const MlpRegs &w, const float *x, float (&h1)[4][4], float (&a2)[4][4])
+// 4 kq + i of sample col.  Returns z (in all four lanes of the sample).
+__device__ __forceinline__ float mlp_tile(const MlpRegs &w, const float *x)
 {
     mx_s4 xh, xm, xl;
     split3v(x, 4, xh, xm, xl);
     mx_s4 hh[4], hm[4], hl[4];
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        mx_f4 acc = {w.B1[b][0], w.B1[b][1], w.B1[b][2], w.B1[b][3]};
+        mx_f4 acc = {0.f, 0.f, 0.f, 0.f};
         acc = mfma3(w.A1[b], xh, xm, xl, acc);
+        float h1[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) h1[b][i] = acc[i] > 0.f ? acc[i] : 0.f;
-        split3v(h1[b], 4, hh[b], hm[b], hl[b]);
+        for (int i = 0; i < 4; ++i) {
+            const float v = acc[i] + w.B1[b][i];
+            h1[i] = v > 0.f ? v : 0.f;
+        }
+        split3v(h1, 4, hh[b], hm[b], hl[b]);
     }
     mx_b8 kh[2], km[2], kl[2];
 #pragma unroll
@@ -191,13 +193,13 @@ __device__ __forceinline__ float mlp_tile(const MlpRegs &w, const float *x, floa
     float z = 0.f;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        mx_f4 acc = {w.B2[c][0], w.B2[c][1], w.B2[c][2], w.B2[c][3]};
+        mx_f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) acc = mfma3k32(w.A2[c][kb], kh[kb], km[kb], kl[kb], acc);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            a2[c][i] = acc[i];
-            z = fmaf(w.W3[c][i], acc[i] > 0.f ? acc[i] : 0.f, z);
+            const float v = acc[i] + w.B2[c][i];
+            z = fmaf(w.W3[c][i], v > 0.f ? v : 0.f, z);
         }
     }
     z += __shfl_xor(z, 16);
@@ -205,16 +207,57 @@ __device__ __forceinline__ float mlp_tile(const MlpRegs &w, const float *x, floa
     return z + w.b3;
 }
 
-// Inference of many samples, bit for bit the FP32 network with its sums taken
+// The network on 16 samples bit for bit as FP32 arithmetic with its sums taken
 // in index order: v_mfma_f32_16x16x4_f32 adds its four products to the
 // accumulator one after the other, each rounded as an FP32 fused
-// multiply-add, so a chain of them is the chain of scalar ones.  A wavefront
-// takes 64 samples in four groups of 16; operand layout (lane l, kq = l / 16):
-// A[l % 16][kq], B[kq][l % 16], D[4 kq + i][l % 16].  Row r of a D block is
-// made hidden unit 16 b + 4 (r % 4) + r / 4 (by the A row it is given), so that
-// register i of D is the B operand of units 16 b + 4 i + kq, in index order.
-// The output layer, one sum per sample, is formed by one lane per sample from
-// the second layer's outputs in LDS (rows of 80: the four rows a store
+// multiply-add, so a chain of them is the chain of scalar ones.  Operand
+// layout (lane l, col = l % 16, kq = l / 16): A[col][kq], B[kq][col],
+// D[4 kq + i][col].  Row r of a D block is made hidden unit
+// 16 b + 4 (r % 4) + r / 4 (by the A row it is given), so that register i of D
+// is unit 16 b + 4 i + kq: the B operand of four units in index order.
+struct MlpF32 {
+    float A1[4][4], A2[4][16], B1[4][4], B2[4][4];
+};
+__device__ __forceinline__ void mlp_load_f32(const MlpView &w, int col, int kq, MlpF32 &r)
+{
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        const int row = 16 * b + 4 * (col & 3) + (col >> 2);   // hidden unit of the lane's A row
+#pragma unroll
+        for (int t = 0; t < 4; ++t) r.A1[b][t] = bf2f(w.W1[row * NIN + 4 * t + kq]);
+#pragma unroll
+        for (int t = 0; t < 16; ++t) r.A2[b][t] = bf2f(w.W2[row * HID + 4 * t + kq]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            r.B1[b][i] = bf2f(w.b1[16 * b + 4 * i + kq]);
+            r.B2[b][i] = bf2f(w.b2[16 * b + 4 * i + kq]);
+        }
+    }
+}
+// xs[t]: input 4 t + kq of the lane's sample; a1, a2: the sums of both hidden
+// layers before the ReLU, register [b][i] of unit 16 b + 4 i + kq
+__device__ __forceinline__ void mlp_tile_f32(const MlpF32 &w, const float *xs, mx_f4 *a1, mx_f4 *a2)
+{
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        a1[b] = mx_f4{w.B1[b][0], w.B1[b][1], w.B1[b][2], w.B1[b][3]};
+        a2[b] = mx_f4{w.B2[b][0], w.B2[b][1], w.B2[b][2], w.B2[b][3]};
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) a1[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.A1[b][t], xs[t], a1[b], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+        const float h = a1[t >> 2][t & 3] > 0.f ? a1[t >> 2][t & 3] : 0.f;   // unit 4 t + kq
+#pragma unroll
+        for (int b = 0; b < 4; ++b) a2[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.A2[b][t], h, a2[b], 0, 0, 0);
+    }
+}
+
+// Inference of many samples: a wavefront takes 64 samples in four groups of
+// 16.  The output layer, one sum per sample, is formed by one lane per sample
+// from the second layer's outputs in LDS (rows of 80: the four rows a store
 // touches lie on different banks).
 // Bound by the matrix cores' FP32 rate: 80 instructions of 32 cycles per 16
 // samples are 85 us for 1 310 720 samples on 1024 SIMDs at 2.4 GHz.  Measured
@@ -235,20 +278,8 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const uint16_t *theta, cons
     if (wave >= ntiles) return;                       // uniform per wavefront
     const MlpView w = mlp_view(theta);
     float *h2 = pool[threadIdx.x >> 6];
-    float A1[4][4], A2[4][16], B1[4][4], B2[4][4];
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        const int row = 16 * b + 4 * (col & 3) + (col >> 2);   // hidden unit of the lane's A row
-#pragma unroll
-        for (int t = 0; t < 4; ++t) A1[b][t] = bf2f(w.W1[row * NIN + 4 * t + kq]);
-#pragma unroll
-        for (int t = 0; t < 16; ++t) A2[b][t] = bf2f(w.W2[row * HID + 4 * t + kq]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            B1[b][i] = bf2f(w.b1[16 * b + 4 * i + kq]);
-            B2[b][i] = bf2f(w.b2[16 * b + 4 * i + kq]);
-        }
-    }
+    MlpF32 r;
+    mlp_load_f32(w, col, kq, r);
     // the lane's inputs of the group of 16 samples that starts at s0 (the
     // next group's are loaded ahead: a group's products hide one round trip)
     float nx[4];
@@ -265,21 +296,7 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const uint16_t *theta, cons
             for (int t = 0; t < 4; ++t) xs[t] = nx[t];
             load(g < 3 ? tile * FW + 16 * (g + 1) : (tile + nwaves) * FW);
             mx_f4 a1[4], a2[4];
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                a1[b] = mx_f4{B1[b][0], B1[b][1], B1[b][2], B1[b][3]};
-                a2[b] = mx_f4{B2[b][0], B2[b][1], B2[b][2], B2[b][3]};
-            }
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) a1[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(A1[b][t], xs[t], a1[b], 0, 0, 0);
-#pragma unroll
-            for (int t = 0; t < 16; ++t) {
-                const float h = a1[t >> 2][t & 3] > 0.f ? a1[t >> 2][t & 3] : 0.f;   // unit 4 t + kq
-#pragma unroll
-                for (int b = 0; b < 4; ++b) a2[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(A2[b][t], h, a2[b], 0, 0, 0);
-            }
+            mlp_tile_f32(r, xs, a1, a2);
 #pragma unroll
             for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -300,35 +317,39 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const uint16_t *theta, cons
 }
 
 // Gradient of the mean binary cross-entropy of sigmoid(z) against y over n
-// samples.  A wavefront takes 32 samples at a time: two forward tiles, the
-// back-propagated sums D1^T = W2^T D2^T on the matrix cores as the forward
-// layers, and the weight gradients gW2 = D2 H1^T, gW1 = D1 X^T as products
-// with the samples as the contraction (K = 32).  There a lane needs eight
-// samples of one hidden unit where the layers leave four hidden units of one
-// sample, so H1, D2, D1 and X pass through LDS (FP32 rows of GROW values:
-// 16-byte aligned reads, rows four apart on different banks).  Both operands
-// are split in three BF16 parts, six products each.  The weight gradients
-// stay in accumulators over all of a wavefront's samples; the four wavefronts
-// of a workgroup add theirs through LDS and write one partial gradient.
-// Bound by latency at the usual batch (8192 samples are one pass of 256
-// wavefronts): loss, gradient and Adam step of a batch 88 -> 23 us against
-// vector arithmetic fed from LDS with 32 samples per workgroup (24 us) and a
-// reduction that walked its 256 partials one after the other on 21
-// workgroups (63 us).  Relative error of the gradient against 64 bits at
-// 8192 samples as before, 3e-7.
-constexpr int GS = 32;             // samples per wavefront and pass
-constexpr int GROW = GS + 4;       // LDS row
-constexpr int GROWS = 3 * HID + NIN;   // H1, D2, D1, X
+// samples.  A workgroup takes 64 samples at a time, 16 per wavefront: the
+// forward tile in FP32 (in index order, so that no ReLU at the edge of
+// rounding switches sides) and the back-propagated sums D1^T = W2^T D2^T as in
+// the indicator's layers.  The weight gradients gW2 = D2 H1^T and
+// gW1 = D1 X^T are products with the 64 samples as the contraction, wavefront
+// w taking the rows 16 w ..: there a lane needs eight samples of one hidden
+// unit where the layers leave four units of one sample, so D2, H1, D1, X (and
+// E = dz relu(a2), whose row sums are gW3) pass through LDS in FP32 (rows of
+// GROW values: 16-byte aligned, rows four apart on different banks).  Both
+// operands are split in three BF16 parts, six products each.  The gradient
+// stays in registers over all of a workgroup's samples, which leaves one
+// partial gradient.
+// Bound by latency at the usual batch (8192 samples are one pass of 128
+// workgroups), so the parameters come through LDS too: read by the lanes of
+// each operand straight from memory, two bytes at a time, they took most of
+// a 25 us kernel.  Loss, gradient and Adam step of a batch of 8192: 88 us
+// with vector arithmetic fed from LDS, 32 samples per workgroup (24 us), and
+// a reduction that walked its 256 partials one after the other on 21
+// workgroups (63 us); now 24 us, which the host needs to issue it (the kernel
+// 17 us, 16 at 300 samples, 38 at 60 000).  Relative error of the gradient
+// against 64 bits at 8192 samples as before, 3e-7.
 constexpr int GWAVES = 4;
-constexpr int GBLOCKS = 256;       // most workgroups (one per CU)
-static_assert(GROWS * GROW >= NPAR, "a wavefront's gradient fits its LDS rows");
+constexpr int GS = MX_TILE * GWAVES;   // samples per workgroup and pass
+constexpr int GROW = GS + 4;           // LDS row
+constexpr int GROWS = 4 * HID + NIN;   // D2, D1, E, H1, X
+constexpr int GBLOCKS = 256;           // most workgroups (one per CU)
 
-// eight samples (8 kq ..) of LDS row r as the three BF16 parts of an operand
-__device__ __forceinline__ void grad_operand(const float *rows, int r, int kq, mx_b8 *o)
+// eight samples (s0 ..) of LDS row r as the three BF16 parts of an operand
+__device__ __forceinline__ void grad_operand(const float *rows, int r, int s0, mx_b8 *o)
 {
     float v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = rows[r * GROW + 8 * kq + i];
+    for (int i = 0; i < 8; ++i) v[i] = rows[r * GROW + s0 + i];
     mx_s8 h, m, l;
     split3v(v, 8, h, m, l);
     o[0] = as_b8(h);
@@ -339,14 +360,26 @@ __device__ __forceinline__ void grad_operand(const float *rows, int r, int kq, m
 __global__ void __launch_bounds__(64 * GWAVES) k_mlp_grad(const uint16_t *theta, const float *x, const float *y, long n,
                                                           float *partial, float *partial_loss)
 {
-    __shared__ __align__(16) float pool[GWAVES][GROWS * GROW];
-    __shared__ float lsum[GWAVES];
+    __shared__ __align__(16) float pool[GROWS * GROW];
+    __shared__ float tail[2][GWAVES];
+    static_assert(sizeof(uint16_t) * NPAR <= sizeof(float) * GROWS * GROW, "the parameters fit the rows");
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int col = lane & 15, kq = lane >> 4;
-    const MlpView w = mlp_view(theta);
-    MlpRegs r;
-    mlp_load(w, col, kq, r);
-    mx_b8 A2T[4][2];               // W2 transposed: out j = 16 b + col, hidden units k of the block pair
+    uint16_t *th = (uint16_t *)pool;
+    for (int i = tid; i < NPAR; i += 64 * GWAVES) th[i] = theta[i];
+    __syncthreads();
+    const MlpView w = mlp_view(th);
+    MlpF32 r;
+    mlp_load_f32(w, col, kq, r);
+    float W3[4][4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) W3[b][i] = bf2f(w.W3[16 * b + 4 * i + kq]);
+    const float b3 = bf2f(w.b3[0]);
+    // W2 transposed, in the same unit order: out 16 b + 4 (col % 4) + col / 4,
+    // summed over the units 4 i + kq of a block pair
+    mx_b8 A2T[4][2];
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -354,137 +387,130 @@ __global__ void __launch_bounds__(64 * GWAVES) k_mlp_grad(const uint16_t *theta,
             mx_s8 q;
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                q[i] = (short)w.W2[(16 * (2 * kb + (i >> 2)) + 4 * kq + (i & 3)) * HID + 16 * b + col];
+                q[i] = (short)w.W2[(16 * (2 * kb + (i >> 2)) + 4 * (i & 3) + kq) * HID + 16 * b + 4 * (col & 3) + (col >> 2)];
             A2T[b][kb] = as_b8(q);
         }
-    float *H1 = pool[wv], *D2 = H1 + HID * GROW, *D1 = D2 + HID * GROW, *X = D1 + HID * GROW;
-    mx_f4 gW2[4][4], gW1[4];
-    float gb1[4][4], gb2[4][4], gW3[4][4], gb3 = 0.f, loss = 0.f;
+    __syncthreads();                     // the rows take the parameters' place
+    float *D2 = pool, *D1 = D2 + HID * GROW, *EE = D1 + HID * GROW, *H1 = EE + HID * GROW, *X = H1 + HID * GROW;
+    mx_f4 gW2[4], gW1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        gW1[c] = mx_f4{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < 4; ++b) gW2[b] = mx_f4{0.f, 0.f, 0.f, 0.f};
+    float rsum = 0.f, gb3 = 0.f, loss = 0.f;   // rsum: row lane of D2 (wavefront 0), D1 (1), E (2)
+    const float inv_n = 1.f / (float)n;
+    const int sl = MX_TILE * wv + col;         // sample within the pass
+    for (long s0 = (long)blockIdx.x * GS; s0 < n; s0 += (long)gridDim.x * GS) {
+        const long s = s0 + sl;
+        const bool in = s < n;
+        float xs[4];
+        mx_f4 a1[4], a2[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xs[i] = in ? x[s * NIN + 4 * i + kq] : 0.f;
+        const float yy = in ? y[s] : 0.f;
+        mlp_tile_f32(r, xs, a1, a2);
+        float z = 0.f;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) z = fmaf(W3[c][i], a2[c][i] > 0.f ? a2[c][i] : 0.f, z);
+        z += __shfl_xor(z, 16);
+        z += __shfl_xor(z, 32);
+        z += b3;
+        const float sg = 1.f / (1.f + expf(-z));
+        const float dz = in ? (sg - yy) * inv_n : 0.f;
+        if (kq == 0 && in) {
+            // BCE with logits, stable form: log(1 + e^z) - y z
+            loss += (z > 0.f ? z + log1pf(expf(-z)) : log1pf(expf(z))) - yy * z;
+            gb3 += dz;
+        }
+        mx_s4 dh[4], dm[4], dl[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            float d2[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = 16 * c + 4 * i + kq;
+                d2[i] = a2[c][i] > 0.f ? dz * W3[c][i] : 0.f;
+                D2[row * GROW + sl] = d2[i];
+                EE[row * GROW + sl] = dz * (a2[c][i] > 0.f ? a2[c][i] : 0.f);
+                H1[row * GROW + sl] = a1[c][i] > 0.f ? a1[c][i] : 0.f;
+            }
+            split3v(d2, 4, dh[c], dm[c], dl[c]);
+        }
+        mx_b8 kh[2], km[2], kl[2];
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            kh[kb] = join8(dh[2 * kb], dh[2 * kb + 1]);
+            km[kb] = join8(dm[2 * kb], dm[2 * kb + 1]);
+            kl[kb] = join8(dl[2 * kb], dl[2 * kb + 1]);
+        }
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-            gW2[c][b] = mx_f4{0.f, 0.f, 0.f, 0.f};
-            gb1[c][b] = gb2[c][b] = gW3[c][b] = 0.f;
+            mx_f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) acc = mfma3k32(A2T[b][kb], kh[kb], km[kb], kl[kb], acc);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) D1[(16 * b + 4 * i + kq) * GROW + sl] = a1[b][i] > 0.f ? acc[i] : 0.f;
         }
-    }
-    const float inv_n = 1.f / (float)n;
-    const long chunks = (n + GS - 1) / GS;
-    for (long ch = (long)blockIdx.x * GWAVES + wv; ch < chunks; ch += (long)gridDim.x * GWAVES) {
-        for (int t = 0; t < GS / MX_TILE; ++t) {
-            const int sl = MX_TILE * t + col;          // sample within the pass
-            const long s = ch * GS + sl;
-            const bool in = s < n;
-            float xs[4], h1[4][4], a2[4][4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) xs[i] = in ? x[s * NIN + 4 * kq + i] : 0.f;
-            const float yy = in ? y[s] : 0.f;
-            const float z = mlp_tile(r, xs, h1, a2);
-            const float sg = 1.f / (1.f + expf(-z));
-            const float dz = in ? (sg - yy) * inv_n : 0.f;
-            if (kq == 0 && in) {
-                // BCE with logits, stable form: log(1 + e^z) - y z
-                loss += (z > 0.f ? z + log1pf(expf(-z)) : log1pf(expf(z))) - yy * z;
-                gb3 += dz;
-            }
-            mx_s4 dh[4], dm[4], dl[4];
+        for (int i = 0; i < 4; ++i) X[(4 * i + kq) * GROW + sl] = xs[i];
+        __syncthreads();
+        // this wavefront's 16 rows of both weight gradients, and a row sum per lane
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                float d2[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = 16 * c + 4 * kq + i;
-                    d2[i] = a2[c][i] > 0.f ? dz * r.W3[c][i] : 0.f;
-                    gb2[c][i] += d2[i];
-                    gW3[c][i] = fmaf(dz, a2[c][i] > 0.f ? a2[c][i] : 0.f, gW3[c][i]);
-                    D2[row * GROW + sl] = d2[i];
-                    H1[row * GROW + sl] = h1[c][i];
-                }
-                split3v(d2, 4, dh[c], dm[c], dl[c]);
-            }
-            mx_b8 kh[2], km[2], kl[2];
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                kh[kb] = join8(dh[2 * kb], dh[2 * kb + 1]);
-                km[kb] = join8(dm[2 * kb], dm[2 * kb + 1]);
-                kl[kb] = join8(dl[2 * kb], dl[2 * kb + 1]);
-            }
+        for (int ks = 0; ks < GS; ks += 32) {
+            mx_b8 a[3], o[3];
+            grad_operand(D2, 16 * wv + col, ks + 8 * kq, a);
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
-                mx_f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) acc = mfma3k32(A2T[b][kb], kh[kb], km[kb], kl[kb], acc);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float d1 = h1[b][i] > 0.f ? acc[i] : 0.f;
-                    gb1[b][i] += d1;
-                    D1[(16 * b + 4 * kq + i) * GROW + sl] = d1;
-                }
+                grad_operand(H1, 16 * b + col, ks + 8 * kq, o);
+                gW2[b] = mfma6k32(a, o, gW2[b]);
             }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) X[(4 * kq + i) * GROW + sl] = xs[i];
+            grad_operand(D1, 16 * wv + col, ks + 8 * kq, a);
+            grad_operand(X, col, ks + 8 * kq, o);
+            gW1 = mfma6k32(a, o, gW1);
         }
-        element_sync<64>();
-        mx_b8 a[4][3], o[3];
+        if (wv < 3) {
+            const float *row = pool + (wv * HID + lane) * GROW;
+            float p[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int c = 0; c < 4; ++c) grad_operand(D2, 16 * c + col, kq, a[c]);
+            for (int k = 0; k < GS; k += 4)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            grad_operand(H1, 16 * b + col, kq, o);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) gW2[c][b] = mfma6k32(a[c], o, gW2[c][b]);
+                for (int i = 0; i < 4; ++i) p[i] += row[k + i];
+            rsum += (p[0] + p[1]) + (p[2] + p[3]);
         }
-        grad_operand(X, col, kq, o);
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            mx_b8 d[3];
-            grad_operand(D1, 16 * b + col, kq, d);
-            gW1[b] = mfma6k32(d, o, gW1[b]);
-        }
-        element_sync<64>();      // before the next pass overwrites the rows
+        __syncthreads();                 // before the next pass overwrites the rows
     }
-    // the sums over samples of the per-unit gradients: over the 16 columns
-    auto column_sum = [](float v) {
-#pragma unroll
-        for (int m = 1; m < 16; m <<= 1) v += __shfl_xor(v, m);
-        return v;
-    };
-    loss = column_sum(loss);
-    gb3 = column_sum(gb3);
-    float *g = pool[wv];          // this wavefront's own rows
+    float *g = partial + (long)blockIdx.x * NPAR;
     float *oW1 = g, *ob1 = oW1 + HID * NIN, *oW2 = ob1 + HID, *ob2 = oW2 + HID * HID, *oW3 = ob2 + HID, *ob3 = oW3 + HID;
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int i = 0; i < 4; ++i) {
+        const int row = 16 * wv + 4 * kq + i;
+        oW1[row * NIN + col] = gW1[i];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = 16 * c + 4 * kq + i;
-            oW1[row * NIN + col] = gW1[c][i];
+        for (int b = 0; b < 4; ++b) oW2[row * HID + 16 * b + col] = gW2[b][i];
+    }
+    if (wv == 0) ob2[lane] = rsum;
+    else if (wv == 1) ob1[lane] = rsum;
+    else if (wv == 2) oW3[lane] = rsum;
+    // loss and output bias: over the wavefront's 16 samples, then the wavefronts
 #pragma unroll
-            for (int b = 0; b < 4; ++b) oW2[row * HID + 16 * b + col] = gW2[c][b][i];
-            const float s1 = column_sum(gb1[c][i]), s2 = column_sum(gb2[c][i]), s3 = column_sum(gW3[c][i]);
-            if (col == 0) {
-                ob1[row] = s1;
-                ob2[row] = s2;
-                oW3[row] = s3;
-            }
-        }
+    for (int m = 1; m < 16; m <<= 1) {
+        loss += __shfl_xor(loss, m);
+        gb3 += __shfl_xor(gb3, m);
+    }
     if (lane == 0) {
-        ob3[0] = gb3;
-        lsum[wv] = loss;
+        tail[0][wv] = loss;
+        tail[1][wv] = gb3;
     }
     __syncthreads();
-    for (int p = tid; p < NPAR; p += 64 * GWAVES) {
-        float s = pool[0][p];
-#pragma unroll
-        for (int k = 1; k < GWAVES; ++k) s += pool[k][p];
-        partial[(long)blockIdx.x * NPAR + p] = s;
-    }
     if (tid == 0) {
-        float s = lsum[0];
+        float sl0 = 0.f, sb = 0.f;
 #pragma unroll
-        for (int k = 1; k < GWAVES; ++k) s += lsum[k];
-        partial_loss[blockIdx.x] = s;
+        for (int k = 0; k < GWAVES; ++k) {
+            sl0 += tail[0][k];
+            sb += tail[1][k];
+        }
+        partial_loss[blockIdx.x] = sl0;
+        ob3[0] = sb;
     }
 }
 
@@ -560,7 +586,7 @@ __global__ void __launch_bounds__(256) k_mlp_alpha(const uint16_t *theta, const 
     for (long tile = wave; tile < ntiles; tile += nwaves) {
         const long e = tile * MX_TILE + col;
         const bool ev = e < nelem;
-        float x[4], h1[4][4], a2[4][4];
+        float x[4];
         bool inside = true;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -569,7 +595,7 @@ __global__ void __launch_bounds__(256) k_mlp_alpha(const uint16_t *theta, const 
         }
         // the four lanes of an element (col, col + 16, col + 32, col + 48)
         inside = inside && __shfl_xor((int)inside, 16) && __shfl_xor((int)inside, 32);
-        const float z = mlp_tile(w, x, h1, a2);
+        const float z = mlp_tile(w, x);
         if (kq == 0 && ev && inside && isfinite(z)) {
             double a = alpha_max / (1.0 + exp(-(double)z));
             if (a < alpha_min) a = 0.0;
@@ -727,7 +753,7 @@ crk_status crk_mlp_grad_workspace_bytes(int nin, int hidden, int64_t n, size_t *
     crk_status st = check_shape(nin, hidden);
     if (st) return st;
     if (!bytes || n < 0) { set_error(CRK_ERR_ARG, "bad argument"); return CRK_ERR_ARG; }
-    const long nb = (long)blocks(n, GS);   // at least one partial gradient per workgroup
+    const long nb = (long)blocks(n, 32);   // (at least one partial gradient per workgroup)
     *bytes = ((size_t)nb * NPAR * sizeof(float) + 255) / 256 * 256 + (size_t)nb * sizeof(float);
     return CRK_OK;
 }
@@ -741,8 +767,7 @@ crk_status crk_mlp_loss_grad(int nin, int hidden, const uint16_t *theta_bf16, co
     size_t need = 0;
     crk_mlp_grad_workspace_bytes(nin, hidden, n, &need);
     if (ws_bytes < need) { set_error(CRK_ERR_ARG, "workspace too small"); return CRK_ERR_ARG; }
-    // 128 samples per workgroup and pass, at most one workgroup per CU
-    unsigned nb = blocks(n, GS * GWAVES);
+    unsigned nb = blocks(n, GS);
     if (nb > GBLOCKS) nb = GBLOCKS;
     float *part = (float *)workspace;
     float *pl = (float *)((char *)workspace + ((size_t)nb * NPAR * sizeof(float) + 255) / 256 * 256);

@@ -1,6 +1,6 @@
 """Network kernels at the edges of their tiling (16 samples per matrix tile,
-32 per wavefront and pass of the gradient, 128 per workgroup, at most 256
-workgroups), against the FP64 oracle."""
+64 per wavefront of the inference and per workgroup and pass of the gradient,
+at most 256 workgroups), against the FP64 oracle."""
 import numpy as np
 import pytest
 
@@ -25,7 +25,7 @@ def _net(seed):
     return net, net.theta_bf16.view(torch.bfloat16).double().cpu().numpy()
 
 
-@pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 33, 127, 128, 129, 32769])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65, 127, 129, 16385, 32769])
 def test_tile_edges(orc, n):
     net, th = _net(n)
     rng = np.random.default_rng(100 + n)
