@@ -1375,6 +1375,10 @@ constexpr int RUN_BLOCK = 256;   // one wavefront per SIMD: no register cap
 template <typename real, int EQ, int DIM, int N, int FLUX, int S, int TAB, bool BLEND>
 __global__ void __launch_bounds__(RUN_BLOCK) k_run(const Tables t, const StepPtrs a0, double *dt_io, int nsteps)
 {
+    static_assert(EQ == EQ_EULER && DIM == 1, "the LDS copies below are laid out for 1D Euler");
+    constexpr int NP = N + 1, M = DIM + 2;
+    constexpr int EMAX = RUN_BLOCK / NP;                    // elements at most
+    constexpr int TR = 2 * DIM * FaceData<EQ, M>::NCT;      // face values per element
     constexpr size_t LB = (size_t)LocalShape<real, EQ, DIM, N, FLUX, BLEND>::slots * RUN_BLOCK * sizeof(real);
     constexpr size_t DB = (size_t)5 * RUN_BLOCK * sizeof(double);
     __shared__ double pool[(LB > DB ? LB : DB) / sizeof(double)];   // local phase, then interface phase
@@ -1392,6 +1396,16 @@ __global__ void __launch_bounds__(RUN_BLOCK) k_run(const Tables t, const StepPtr
     }
     if (tid == 0) { dtl[0] = dt_io[0]; dtl[1] = dt_io[1]; }
     __syncthreads();
+    StepPtrs p{};
+    p.dt = dtl;
+    p.dt_out = dtl;                    // (non-null: the interface phase runs its tail)
+    p.traces = trl;
+    p.partials = &smax;
+    if constexpr (BLEND) {
+        p.alpha_raw = araw;
+        p.alpha_raw_out = araw;
+        p.alpha_s = asm_;
+    }
     for (int k = 0; k < nsteps; ++k) {
         p.u_in = ub + (k & 1 ? len : 0);
         p.u_out = ub + (k & 1 ? 0 : len);
@@ -1401,6 +1415,17 @@ __global__ void __launch_bounds__(RUN_BLOCK) k_run(const Tables t, const StepPtr
         __syncthreads();
         if (tid == 0) finish_dt(t, smax, EQ == EQ_MHD ? 1 : 0, dtl);
         __syncthreads();
+    }
+    for (int i = tid; i < len; i += RUN_BLOCK) {
+        g0[i] = ub[i];
+        g1[i] = ub[len + i];
+    }
+    for (int i = tid; i < TR * E; i += RUN_BLOCK) gt[i] = trl[i];
+    if constexpr (BLEND) {
+        for (int i = tid; i < E; i += RUN_BLOCK) {
+            const_cast<double *>(a0.alpha_raw)[i] = araw[i];
+            a0.alpha_s[i] = asm_[i];
+        }
     }
     if (tid == 0) { dt_io[0] = dtl[0]; dt_io[1] = dtl[1]; }
 }
@@ -1414,10 +1439,6 @@ __global__ void __launch_bounds__(BLOCK) k_dt_partial(const Tables t, const void
     using Phys = typename PhysOf<real, EQ, DIM, (EQ == EQ_MHD ? VOL_DERIGS : VOL_KG)>::type;
     constexpr int M = Phys::M;
     __shared__ double red[BLOCK];
-    static_assert(EQ == EQ_EULER && DIM == 1, "the LDS copies below are laid out for 1D Euler");
-    constexpr int NP = N + 1, M = DIM + 2;
-    constexpr int EMAX = RUN_BLOCK / NP;                    // elements at most
-    constexpr int TR = 2 * DIM * FaceData<EQ, M>::NCT;      // face values per element
     const real *u = (const real *)u_;
     const long total = (long)t.nelem * t.nnode;
     Ctx<real> ctx = make_ctx<real>(t, nullptr);
@@ -1430,16 +1451,6 @@ __global__ void __launch_bounds__(BLOCK) k_dt_partial(const Tables t, const void
         double s = 0.0;
 #pragma unroll
         for (int d = 0; d < DIM; ++d) {
-    StepPtrs p{};
-    p.dt = dtl;
-    p.dt_out = dtl;                    // (non-null: the interface phase runs its tail)
-    p.traces = trl;
-    p.partials = &smax;
-    if constexpr (BLEND) {
-        p.alpha_raw = araw;
-        p.alpha_raw_out = araw;
-        p.alpha_s = asm_;
-    }
             if constexpr (EQ == EQ_MHD) s = fmax(s, (double)MhdP<real, VOL_DERIGS>::fast(d, nd, ctx));
             else s += (double)Phys::speed(d, nd, ctx) * t.invdx[d];
         }
@@ -1449,17 +1460,6 @@ __global__ void __launch_bounds__(BLOCK) k_dt_partial(const Tables t, const void
     __syncthreads();
     for (int w = BLOCK / 2; w > 0; w >>= 1) {
         if (threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
-    for (int i = tid; i < len; i += RUN_BLOCK) {
-        g0[i] = ub[i];
-        g1[i] = ub[len + i];
-    }
-    for (int i = tid; i < TR * E; i += RUN_BLOCK) gt[i] = trl[i];
-    if constexpr (BLEND) {
-        for (int i = tid; i < E; i += RUN_BLOCK) {
-            const_cast<double *>(a0.alpha_raw)[i] = araw[i];
-            a0.alpha_s[i] = asm_[i];
-        }
-    }
         __syncthreads();
     }
     if (threadIdx.x == 0) partials[blockIdx.x] = red[0];
