@@ -141,12 +141,10 @@ namespace {
 
 // Tile flags (pipelined step with the limiter, 2D, Kennedy-Gruber or
 // Ranocha flux; the learned indicator flags from its own coefficients as
-// well): flagged-clear tiles take the local-phase instance without the
-// blending code, whose register count allows a fourth wavefront per SIMD in
-// FP64 with Kennedy-Gruber (120 instead of 156 VGPRs) and a seventh in FP32;
-// with the Ranocha flux it stays at three wavefronts in FP64 but issues 6 %
-// fewer instructions (77 instead of 83 us on the 256^2 KHI state), a little
-// more than the nearly empty second launch costs.  A 1D mesh small enough
+// well): flagged-clear tiles take the local-phase code without the blending
+// code, which issues 6 % fewer instructions and, launched on its own, needs
+// fewer registers (Kennedy-Gruber FP64 120 instead of 156 VGPRs: a fourth
+// wavefront per SIMD; see one_local_launch).  A 1D mesh small enough
 // for crk_run's single launch keeps the blending instance so that both give
 // the same bits.
 bool use_tile_flags(const crk_solver *s)
@@ -702,6 +700,7 @@ crk_status crk_advance(crk_solver *s, const void *u_in, void *u_out, double *dt_
     if (instances) {
         StepPtrs p{};
         p.instances = instances;
+        p.learned = s->mlp != nullptr;
         p.u_in = u_in; p.u_out = u_out; p.dt = dt_dev; p.traces = tr;
         p.stage_tr = s->stagewise ? s->ws + s->off_stage : nullptr;
         p.alpha_raw = lim ? araw : nullptr;

@@ -184,6 +184,7 @@ struct StepPtrs {
     // blending code, bit 1 the one with it (0: both); either launches only
     // where the configuration uses it
     int instances;
+    int learned;   // local phase: the coefficients come from the learned indicator
     // MHD with the stage-wise non-conservative interface flux: the stage
     // states u^(j) at the face nodes, [face][j][v][e][k] (local phase
     // writes, interface phase reads); nullptr: the reduced form
@@ -940,6 +941,27 @@ k_local(const Tables t, const StepPtrs a)
                                                                WPB == 1 ? -1 : (int)(threadIdx.x % 64));
 }
 
+// Both kinds of tile in one launch: every tile takes the code of its flag,
+// at the blending instance's register count.  Same tile code, same bits.
+template <typename real, int DIM, int N, int FLUX, int S, int TAB, int WPB>
+__global__ void __launch_bounds__(tile_block<DIM == 2 ? (N + 1) * (N + 1) : N + 1>() * WPB)
+k_local_any(const Tables t, const StepPtrs a)
+{
+    constexpr int NP = DIM == 2 ? (N + 1) * (N + 1) : N + 1;
+    constexpr int TB = tile_block<NP>();
+    constexpr int SB = LocalShape<real, EQ_EULER, DIM, N, FLUX, true>::slots, SP = LocalShape<real, EQ_EULER, DIM, N, FLUX, false>::slots;
+    constexpr int SL = (SB > SP ? SB : SP) * TB;
+    __shared__ real smem[SL * WPB];
+    const int w = WPB == 1 ? 0 : (int)(threadIdx.x / 64);
+    const long tile = (long)xcd_chunk_tile(blockIdx.x, gridDim.x) * WPB + w;
+    if (tile * (TB / NP) >= t.nelem) return;
+    const int flagged = __builtin_amdgcn_readfirstlane(a.tiles_in[tile]);
+    if (threadIdx.x % 64 == 0) a.tiles_out[tile] = 0;
+    const int lane = WPB == 1 ? -1 : (int)(threadIdx.x % 64);
+    if (flagged) local_tile<real, EQ_EULER, DIM, N, FLUX, S, TB, TAB, true>(t, a, tile * (TB / NP), smem + w * SL, lane);
+    else local_tile<real, EQ_EULER, DIM, N, FLUX, S, TB, TAB, false>(t, a, tile * (TB / NP), smem + w * SL, lane);
+}
+
 // ---------------------------------------------------------------- K8 helper: modal indicator
 // Blending coefficient of one element from eps = rho*p at its nodes, one lane
 // per node: modal coefficients in the orthonormal Legendre basis, energy in
@@ -1654,6 +1676,30 @@ static __global__ void k_diag_final(int M, const double *partials, int nparts, d
 }
 
 // ---------------------------------------------------------------- launchers
+// Tile flags: both kinds of tile in one launch (k_local_any), or one launch
+// per kind.  The second launch costs 4 us and more with the mesh even where
+// it skips every tile, and two launches in sequence leave the chip half idle
+// at each one's end; what they buy is the fourth (FP32: sixth and seventh)
+// wavefront per SIMD of the Kennedy-Gruber tiles that cannot blend, at
+// degrees 2 and 3.  us per step, two launches / one, no tile blends | 95 %
+// blend | half do (KHI n^2, degree 3, Kennedy-Gruber):
+//   FP64 64: 20.8/18.3 | 21.6/19.7; 128: 32.8/31.4 | 39.1/35.2 | 42.7/34.8;
+//        256: 67.6/67.1 | 80.0/75.0 | 85.0/74.8; 320: 91/93 | 115/109;
+//        512: 245/257 | 307/293 | 288/279; 1000: 888/949 | 1131/1094 | 1019/1020
+//   FP32 64: 19.6/16.9 | 20.0/17.2; 256: 49.5/47.1 | 58.3/52.2 | 61/50;
+//        512: 132/130 | 170/161 | 160/149; 1000: 524/544 | 700/658 | 621/606
+// so two launches where a mesh has more than 16 wavefronts per SIMD in FP64
+// (256^2), 64 in FP32 (512^2) -- except with a learned indicator, which is
+// bound where tiles do blend (512^2 FP64 325/306, FP32 185/174).  Elsewhere
+// the instances differ by a wavefront at most: Ranocha 256^2 FP64 93.9/92.7 |
+// 112/106, 1000^2 1341/1350 | 1566/1535; degree 4 400^2 FP64 392/384 |
+// 428/420; degree 1 1024^2 FP64 393/377: one launch.
+template <typename real, int N, int FLUX>
+inline bool one_local_launch(long waves, const StepPtrs &p)
+{
+    if (FLUX != VOL_KG || N == 1 || N == 4 || p.learned) return true;
+    return waves <= 1024 * (sizeof(real) == 8 ? 16 : 64);
+}
 template <typename real, int EQ, int DIM, int N, int FLUX>
 hipError_t launch_local(const Tables &t, const StepPtrs &p, hipStream_t s)
 {
@@ -1699,6 +1745,29 @@ hipError_t launch_local(const Tables &t, const StepPtrs &p, hipStream_t s)
     }
     const bool blend = p.alpha != nullptr || p.alpha_raw != nullptr;
     const int which = p.instances ? p.instances : 3;
+    if constexpr (EQ == EQ_EULER && DIM == 2 && FLUX != VOL_CENTRAL) {
+        if (blend && p.tiles_in != nullptr && one_local_launch<real, N, FLUX>((long)grid * (TB / 64), p)) {
+            // (issued separately, both kinds of tile belong to the first launch)
+            if (!(which & 1)) return hipSuccess;
+            const dim3 g((grid + WB - 1) / WB), b(TB * WB);
+            switch (t.stages) {
+            case 1: hipLaunchKernelGGL((k_local_any<real, DIM, N, FLUX, 1, 0, WB>), g, b, 0, s, t, p); break;
+            case 2: hipLaunchKernelGGL((k_local_any<real, DIM, N, FLUX, 2, 0, WB>), g, b, 0, s, t, p); break;
+            case 3: hipLaunchKernelGGL((k_local_any<real, DIM, N, FLUX, 3, 0, WB>), g, b, 0, s, t, p); break;
+            case 4:
+                if (t.tableau == 1) hipLaunchKernelGGL((k_local_any<real, DIM, N, FLUX, 4, 1, WB>), g, b, 0, s, t, p);
+                else hipLaunchKernelGGL((k_local_any<real, DIM, N, FLUX, 4, 0, WB>), g, b, 0, s, t, p);
+                break;
+            case 5: hipLaunchKernelGGL((k_local_any<real, DIM, N, FLUX, 5, 0, WB>), g, b, 0, s, t, p); break;
+            case 6:
+                if (t.tableau == 2) hipLaunchKernelGGL((k_local_any<real, DIM, N, FLUX, 6, 2, WB>), g, b, 0, s, t, p);
+                else hipLaunchKernelGGL((k_local_any<real, DIM, N, FLUX, 6, 0, WB>), g, b, 0, s, t, p);
+                break;
+            default: return hipErrorInvalidValue;
+            }
+            return hipGetLastError();
+        }
+    }
     if ((which & 1) && (!blend || p.tiles_in != nullptr)) {
         CRK_LOCAL_LAUNCH(false, WP)
         hipError_t e = hipGetLastError();
