@@ -3,6 +3,7 @@
 #pragma once
 #include "crk_dispatch.hpp"
 #include "crk_rhs.hpp"
+#include "crk_split.hpp"
 
 namespace crk {
 

@@ -374,7 +374,7 @@ struct LocalShape {
     static constexpr bool SYM = N >= 2;
     static constexpr int NPRIM = SYM ? (n1 - 1) / 2 : 0;           // rotations whose mirror comes from LDS
     static constexpr int KSELF = (SYM && n1 % 2 == 0) ? n1 / 2 : 0;  // self-mirrored rotation, evaluated directly
-    static constexpr int NX = SYM ? DIM * NPRIM * Phys::M : 0;
+    static constexpr int NX = SYM ? DIM * NPRIM * Phys::MX : 0;
     // ASL slots carry the blending coefficients of each element and of its
     // face neighbours ((2 DIM + 1) values per element of NP lanes; only in
     // the instance with the blending code)
@@ -668,7 +668,8 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
         real *lds = lds0 + ((DBF && (i & 1)) ? NF * BLK : 0);
         if (i > 0 && !DBF) element_sync<NP, BLK>();    // the previous stage has finished reading LDS
 #pragma unroll
-        for (int f = 0; f < NF; ++f) lds[f * BLK + tid] = nd[f];
+        for (int f = 0; f < NF; ++f)
+            if (Phys::paired(f)) lds[f * BLK + tid] = nd[f];
         element_sync<NP, BLK>();
         if (i == 0) {
             if (blend && valid) alpha = alds[le * NA];
@@ -716,16 +717,20 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
                 const int q = line_node<N, DIM>(pd, d, qd);
                 real ndq[NF];
 #pragma unroll
-                for (int f = 0; f < NF; ++f) ndq[f] = lds[f * BLK + base + q];
+                for (int f = 0; f < NF; ++f)
+                    if (Phys::paired(f)) ndq[f] = lds[f * BLK + base + q];
                 real fs[M];
                 Phys::pair(d, nd, ndq, fs, ctx);
                 const real ck = dk(d, k);
 #pragma unroll
-                for (int v = 0; v < M; ++v) R[v] += ck * fs[v];
+                for (int v = 0; v < M; ++v)
+                    if (Phys::pairs(d, v)) R[v] += ck * fs[v];
                 if constexpr (SYM) {
                     if (k <= NPRIM) {
 #pragma unroll
-                        for (int v = 0; v < M; ++v) xch[((d * NPRIM + (k - 1)) * M + v) * BLK + tid] = fs[v];
+                        for (int v = 0; v < M; ++v)
+                            if (Phys::pairs(d, v))
+                                xch[((d * NPRIM + (k - 1)) * Phys::MX + Phys::xidx(d, v)) * BLK + tid] = fs[v];
                     }
                 }
             }
@@ -738,7 +743,7 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
                 const real gp = bi * oafh[d], gw = bi * cF[d], c0 = dk(d, 0);
 #pragma unroll
                 for (int v = 0; v < M; ++v) {
-                    R[v] += c0 * fp[v];
+                    if (Phys::pairs(d, v)) R[v] += c0 * fp[v];
                     P[d][v] += gp * fp[v];
                     W[v] -= gw * fp[v];
                 }
@@ -775,6 +780,10 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
                 MhdP<real, FLUX>::btimes(d, nd, gB, gpsi, o);
 #pragma unroll
                 for (int v = 0; v < M; ++v) R[v] += o[v];
+                if constexpr (Phys::LEAN) {
+                    R[8] += ctx.ch * gB;
+                    R[5 + d] += ctx.ch * gpsi;
+                }
             }
             // first-order subcell fluxes of the blending limiter, from u^n = u^(1)
             if (i == 0 && blend && alpha > real(0)) {
@@ -847,7 +856,9 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
                     const int src = base + line_node<N, DIM>(pd, d, sd);
                     const real c = dk(d, n1 - k);
 #pragma unroll
-                    for (int v = 0; v < M; ++v) R[v] += c * xch[((d * NPRIM + (k - 1)) * M + v) * BLK + src];
+                    for (int v = 0; v < M; ++v)
+                        if (Phys::pairs(d, v))
+                            R[v] += c * xch[((d * NPRIM + (k - 1)) * Phys::MX + Phys::xidx(d, v)) * BLK + src];
                 }
         }
         // stage bookkeeping
@@ -1676,6 +1687,23 @@ static __global__ void k_diag_final(int M, const double *partials, int nparts, d
 }
 
 // ---------------------------------------------------------------- launchers
+// GLM-MHD local stages in FP64 with two lanes per node (crk_split.hpp) or
+// one.  Two lanes halve what a wavefront carries, so a second wavefront per
+// SIMD fits and a mesh that leaves SIMDs idle gets twice the wavefronts; the
+// price is one more barrier per stage and exchange through LDS.  us per step,
+// one / two lanes per node, n^2 elements (n = 24, 48, 96, 192, 320):
+//   degree 4: 33/28 39/40 113/109 373/346 1000/943: two lanes;
+//   degree 2: 22/20 23/22 40/39 96/92 219/217: two lanes;
+//   degree 3: 21/19 25/26 59/52 152/155 392/394: two up to four one-lane
+//     wavefronts per SIMD (192^2 is nine);
+//   degree 1 (no mirrored pairs to share): 24/30 at 96^2: one.
+// FP32 has its second and third wavefront anyway (degree 4 176/179, degree 3
+// 71/81, degree 2 49/52 at 192^2).
+template <typename real, int N>
+constexpr bool split_always() { return sizeof(real) == 8 && (N == 2 || N == 4); }
+template <typename real, int N>
+constexpr bool split_ever() { return sizeof(real) == 8 && N > 1; }
+constexpr long SPLIT_WAVES = 4 * 1024;
 // Tile flags: both kinds of tile in one launch (k_local_any), or one launch
 // per kind.  The second launch costs 4 us and more with the mesh even where
 // it skips every tile, and two launches in sequence leave the chip half idle
@@ -1700,8 +1728,11 @@ inline bool one_local_launch(long waves, const StepPtrs &p)
     if (FLUX != VOL_KG || N == 1 || N == 4 || p.learned) return true;
     return waves <= 1024 * (sizeof(real) == 8 ? 16 : 64);
 }
+template <typename real, int N, int FLUX>
+hipError_t launch_local_split(const Tables &t, const StepPtrs &p, hipStream_t s);
+
 template <typename real, int EQ, int DIM, int N, int FLUX>
-hipError_t launch_local(const Tables &t, const StepPtrs &p, hipStream_t s)
+hipError_t launch_local_one(const Tables &t, const StepPtrs &p, hipStream_t s)
 {
     constexpr int NP = DIM == 2 ? (N + 1) * (N + 1) : N + 1;
     constexpr int TB = tile_block<NP>();
@@ -1727,9 +1758,6 @@ hipError_t launch_local(const Tables &t, const StepPtrs &p, hipStream_t s)
         default: return hipErrorInvalidValue;                                                                      \
         }                                                                                                          \
     }
-    // without blending coefficients (no limiter) every tile takes the
-    // instance without the blending code; with tile flags both run, the
-    // blending one second; with given coefficients only the blending one
     if constexpr (EQ == EQ_MHD) {
         if (p.stage_tr != nullptr) {
             // stage-wise non-conservative interface flux: the default tableaus only
@@ -1743,6 +1771,9 @@ hipError_t launch_local(const Tables &t, const StepPtrs &p, hipStream_t s)
             return hipGetLastError();
         }
     }
+    // without blending coefficients (no limiter) every tile takes the
+    // instance without the blending code; with tile flags both run, the
+    // blending one second; with given coefficients only the blending one
     const bool blend = p.alpha != nullptr || p.alpha_raw != nullptr;
     const int which = p.instances ? p.instances : 3;
     if constexpr (EQ == EQ_EULER && DIM == 2 && FLUX != VOL_CENTRAL) {
@@ -1780,6 +1811,21 @@ hipError_t launch_local(const Tables &t, const StepPtrs &p, hipStream_t s)
     }
 #undef CRK_LOCAL_LAUNCH
     return hipGetLastError();
+}
+
+template <typename real, int EQ, int DIM, int N, int FLUX>
+hipError_t launch_local(const Tables &t, const StepPtrs &p, hipStream_t s)
+{
+    if constexpr (EQ == EQ_MHD && split_always<real, N>()) {
+        return launch_local_split<real, N, FLUX>(t, p, s);
+    } else {
+        if constexpr (EQ == EQ_MHD && split_ever<real, N>()) {
+            constexpr int EPB = tile_block<(N + 1) * (N + 1)>() / ((N + 1) * (N + 1));
+            const long waves = (long)((t.nelem + EPB - 1) / EPB) * (tile_block<(N + 1) * (N + 1)>() / 64);
+            if (waves <= SPLIT_WAVES) return launch_local_split<real, N, FLUX>(t, p, s);
+        }
+        return launch_local_one<real, EQ, DIM, N, FLUX>(t, p, s);
+    }
 }
 
 inline hipError_t launch_zero_int(int *p, int n, hipStream_t s)

@@ -151,6 +151,11 @@ struct EulerP {
     static constexpr int NF = (FLUX == VOL_RANOCHA) ? DIM + 5 : DIM + 3;
     static constexpr int P = DIM + 1;
     static constexpr bool HALF = (FLUX == VOL_KG);
+    // every field is read by pair(), every variable has a pair flux
+    static constexpr int MX = M;
+    __device__ __forceinline__ static constexpr bool paired(int) { return true; }
+    __device__ __forceinline__ static constexpr bool pairs(int, int) { return true; }
+    __device__ __forceinline__ static constexpr int xidx(int, int v) { return v; }
 
     // fields from the conserved state; with logs = false the logarithms of
     // the Ranocha flux are skipped (enough for phys, speed, cons)
@@ -336,6 +341,23 @@ template <typename real, int FLUX>
 struct MhdP {
     static constexpr int M = 9;
     static constexpr int NF = 15;
+    // FP64, bound by LDS and registers: fewer fields and fluxes are exchanged
+    // between the lanes.  (In FP32 that gained 0 to 3 %; it keeps the plain
+    // form and its rounding.)
+    static constexpr bool LEAN = sizeof(real) == 8;
+    // the fields that pair() reads of either state (the Derigs flux forms
+    // what it needs of |B|^2 itself)
+    __device__ __forceinline__ static constexpr bool paired(int f)
+    {
+        return !LEAN || (FLUX == VOL_CENTRAL ? (f < 9 || f > 11) : (f != 4 && f < 12));
+    }
+    // The fluxes of the normal field B_d and psi, c_h times an arithmetic
+    // mean, need no pairs in a volume term: the rows of D sum to zero, so
+    // their residuals are c_h sum_q D_pq psi_q and c_h sum_q D_pq B_d,q, the
+    // sums of the non-conservative term.  MX variables are left (index xidx).
+    static constexpr int MX = LEAN ? M - 2 : M;
+    __device__ __forceinline__ static constexpr bool pairs(int d, int v) { return !LEAN || (v != 8 && v != 5 + d); }
+    __device__ __forceinline__ static constexpr int xidx(int d, int v) { return LEAN && v > 5 + d ? v - 1 : v; }
 
     __device__ __forceinline__ static void node(const real *u, real *nd, const Ctx<real> &c)
     {
@@ -437,19 +459,46 @@ struct MhdP {
         real va[3], Ba[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) { va[k] = h * (a[1 + k] + b[1 + k]); Ba[k] = h * (a[5 + k] + b[5 + k]); }
-        const real f0 = rho_ln * va[d];
+        if constexpr (!LEAN) {
+            const real f0 = rho_ln * va[d];
+            f[0] = f0;
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                f[1 + k] = f0 * va[k] - Ba[d] * Ba[k] + (k == d ? rho_a * i2b + h * h * (a[13] + b[13]) : real(0));
+#pragma unroll
+            for (int k = 0; k < 3; ++k) f[5 + k] = (k == d) ? c.ch * psi_a : va[d] * Ba[k] - va[k] * Ba[d];
+            f[8] = c.ch * Ba[d];
+            f[4] = f0 * (h * c.inv_gm1 * ibeta_ln - h * h * (a[12] + b[12]))
+                 + f[1] * va[0] + f[2] * va[1] + f[3] * va[2]
+                 + f[5] * Ba[0] + f[6] * Ba[1] + f[7] * Ba[2] + f[8] * psi_a
+                 - h * h * (a[1 + d] * a[13] + b[1 + d] * b[13]) + Ba[d] * h * (a[14] + b[14])
+                 - c.ch * h * (a[5 + d] * a[8] + b[5 + d] * b[8]);
+            return;
+        }
+        real BBa = real(0), BBb = real(0), BaBb = real(0), vavb = real(0), cross = real(0);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            BBa += a[5 + k] * a[5 + k];
+            BBb += b[5 + k] * b[5 + k];
+            BaBb += a[5 + k] * b[5 + k];
+            vavb += a[1 + k] * b[1 + k];
+            cross += a[1 + k] * b[5 + k] + b[1 + k] * a[5 + k];
+        }
+        const real f0 = rho_ln * va[d], pd = rho_a * i2b;
         f[0] = f0;
 #pragma unroll
         for (int k = 0; k < 3; ++k)
-            f[1 + k] = f0 * va[k] - Ba[d] * Ba[k] + (k == d ? rho_a * i2b + h * h * (a[13] + b[13]) : real(0));
+            f[1 + k] = f0 * va[k] - Ba[d] * Ba[k] + (k == d ? pd + h * h * (BBa + BBb) : real(0));
 #pragma unroll
         for (int k = 0; k < 3; ++k) f[5 + k] = (k == d) ? c.ch * psi_a : va[d] * Ba[k] - va[k] * Ba[d];
         f[8] = c.ch * Ba[d];
-        f[4] = f0 * (h * c.inv_gm1 * ibeta_ln - h * h * (a[12] + b[12]))
-             + f[1] * va[0] + f[2] * va[1] + f[3] * va[2]
-             + f[5] * Ba[0] + f[6] * Ba[1] + f[7] * Ba[2] + f[8] * psi_a
-             - h * h * (a[1 + d] * a[13] + b[1 + d] * b[13]) + Ba[d] * h * (a[14] + b[14])
-             - c.ch * h * (a[5 + d] * a[8] + b[5 + d] * b[8]);
+        // The energy flux f0 (1/(2 (gamma - 1) beta_ln) - mean |v|^2 / 2) + sum_k f_{v_k} mean v_k
+        // + sum_k f_{B_k} mean B_k + f_psi mean psi - mean(v_d |B|^2) / 2 + mean B_d mean(v.B)
+        // - c_h mean(B_d psi) with the products of means multiplied out: the squares of each
+        // state's own velocity and its v.B cancel, which leaves products of the two states only.
+        f[4] = f0 * (h * c.inv_gm1 * ibeta_ln + h * vavb) + pd * va[d]
+             + h * h * (a[1 + d] * BBb + b[1 + d] * BBa) + h * va[d] * BaBb
+             - h * Ba[d] * cross + h * c.ch * (a[5 + d] * b[8] + b[5 + d] * a[8]);
     }
 };
 

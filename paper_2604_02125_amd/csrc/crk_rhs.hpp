@@ -18,7 +18,7 @@ enum { SURF_RUSANOV = 0, SURF_EC = 1 };
 template <typename real, int EQ, int DIM, int N, int FLUX>
 struct RhsShape {
     using L = LocalShape<real, EQ, DIM, N, FLUX>;
-    static constexpr int slots = L::Phys::NF + L::NX;
+    static constexpr int slots = L::Phys::NF + (L::SYM ? DIM * L::NPRIM * L::Phys::M : 0);
 };
 
 // Semi-discrete FR residual of one node (one lane): R = volume term of
