@@ -978,14 +978,45 @@ k_local_any(const Tables t, const StepPtrs a)
 // per node: modal coefficients in the orthonormal Legendre basis, energy in
 // the highest modes, logistic map (Hennemann-Gassner form), clipping at
 // alpha_min and cap at alpha_max.  Every lane of the workgroup must call it.
+// a double moved across lanes by a DPP control (CTRL a compile-time control
+// word; every source lane exists for the quad permutations, row rotations and
+// mirrors used here)
+template <int CTRL>
+__device__ __forceinline__ double dpp_double(double x)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+
 // sum over the aligned groups of W consecutive lanes of a wavefront (W a
-// power of two dividing 64); every lane of a group gets the same bits
+// power of two dividing 64); every lane of a group gets the same bits.  Up to
+// 16 lanes by DPP: pairs and quads by quad permutations, then, the sums being
+// equal within a quad (half row), the mirrored half row (row) stands for the
+// lane 4 (8) away.
 template <int W>
 __device__ __forceinline__ double group_sum(double x)
 {
+    if constexpr (W >= 2) x += dpp_double<0xB1>(x);     // quad_perm 1 0 3 2
+    if constexpr (W >= 4) x += dpp_double<0x4E>(x);     // quad_perm 2 3 0 1
+    if constexpr (W >= 8) x += dpp_double<0x141>(x);    // row_half_mirror
+    if constexpr (W >= 16) x += dpp_double<0x140>(x);   // row_mirror
 #pragma unroll
-    for (int m = 1; m < W; m <<= 1) x += __shfl_xor(x, m, W);
+    for (int m = 16; m < W; m <<= 1) x += __shfl_xor(x, m, W);
     return x;
+}
+// maximum over the wavefront, in every lane
+__device__ __forceinline__ double wave_max(double x)
+{
+    x = fmax(x, dpp_double<0xB1>(x));
+    x = fmax(x, dpp_double<0x4E>(x));
+    x = fmax(x, dpp_double<0x141>(x));
+    x = fmax(x, dpp_double<0x140>(x));
+    auto row = [&](int lane) {
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                                __builtin_amdgcn_readlane(__double2loint(x), lane));
+    };
+    return fmax(fmax(row(0), row(16)), fmax(row(32), row(48)));
 }
 
 // Flag the local-phase tiles (epb elements each) of element e, of its face
@@ -1023,17 +1054,6 @@ __device__ __forceinline__ double indicator_eps(const double *us, double gamma)
     for (int k = 0; k < DIM; ++k) ke += us[1 + k] * us[1 + k];
     const double p = (gamma - 1.0) * (us[DIM + 1] - 0.5 * ke / us[0]);
     return us[0] * p;
-}
-
-// a double moved across lanes by a DPP control (CTRL a compile-time control
-// word; every source lane exists for the quad permutations and the row
-// rotations used here)
-template <int CTRL>
-__device__ __forceinline__ double dpp_double(double x)
-{
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xF, 0xF, false);
-    return __hiloint2double(hi, lo);
 }
 
 template <int DIM, int N, int BLK>
@@ -1174,11 +1194,10 @@ __device__ __forceinline__ void indicator_lanes(const Tables &t, int tid, int le
 template <int BLK, bool ATOMIC = false>
 __device__ __forceinline__ void block_max_lanes(double v, double *red, double *slot)
 {
-    // maximum over the wavefront by butterfly, then over the BLK/64 wavefronts
+    // maximum over the wavefront, then over the BLK/64 wavefronts
     static_assert(BLK % 64 == 0, "whole wavefronts");
     const int tid = threadIdx.x;
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v = fmax(v, __shfl_xor(v, m, 64));
+    v = wave_max(v);
     if constexpr (BLK > 64) {
         if ((tid & 63) == 0) red[tid >> 6] = v;
         __syncthreads();
@@ -1270,6 +1289,27 @@ __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &
             for (int v = 0; v < M; ++v) uno[v] = uin[((long)v * E + e) * NP + node];
             Phys::node_basic(uno, ndo, ctx);
         }
+        // both directions' shares are loaded before either is used: one round
+        // trip to memory instead of two (not for FP32 MHD, whose sums then
+        // contract into other fused multiply-adds).  With the reductions of
+        // the tail by DPP instead of LDS permutes: ten steps of KHI 256^2 FP64
+        // 676 -> 663 us, eight of 1000 x 1024 FP32 4541 -> 4416 us.
+        constexpr bool TOGETHER = EQ == EQ_EULER || sizeof(real) == 8;
+        constexpr int NL = EQ == EQ_MHD && !NCS ? M + 2 : M;
+        real share[DIM][NL];
+#pragma unroll
+        for (int d = 0; TOGETHER && d < DIM; ++d) {
+            if (!(pd[d] == 0 || pd[d] == N)) continue;
+            const int side = pd[d] == N ? 1 : 0;
+            const long en = side ? nb.n[d][1] : nb.n[d][0];
+            const int nface = 2 * d + 1 - side;
+            const int kk = DIM == 1 ? 0 : (d == 0 ? pd[1] : pd[0]);
+            const bool wl = W && ((nb.wall >> (2 * d + side)) & 1);
+            const real *tn = wl ? tr + ((long)(2 * d + side) * FD::NCT * E + e) * nf + kk
+                                : tr + ((long)nface * FD::NCT * E + en) * nf + kk;
+#pragma unroll
+            for (int v = 0; v < NL; ++v) share[d][v] = tn[((long)v * E) * nf];
+        }
 #pragma unroll
         for (int d = 0; d < DIM; ++d) {
             if (!(pd[d] == 0 || pd[d] == N)) continue;
@@ -1287,15 +1327,18 @@ __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &
             real jump[M];
 #pragma unroll
             for (int v = 0; v < M; ++v) {
-                const real x = tn[((long)v * E) * nf];
+                const real x = TOGETHER ? share[d][v] : tn[((long)v * E) * nf];
                 jump[v] = (wl && v != 1 + d) ? -x : x;
             }
             if constexpr (EQ == EQ_MHD) {
                 if constexpr (!NCS) {
                     // reduced form: the neighbour's half of 1/2 B(u^n)(g(U^-) + g(U^+))
                     real o[M];
-                    MhdP<real, FLUX>::btimes(d, ndo, real(0.5) * tn[((long)M * E) * nf],
-                                             real(0.5) * tn[((long)(M + 1) * E) * nf], o);
+                    if constexpr (TOGETHER)
+                        MhdP<real, FLUX>::btimes(d, ndo, real(0.5) * share[d][M], real(0.5) * share[d][M + 1], o);
+                    else
+                        MhdP<real, FLUX>::btimes(d, ndo, real(0.5) * tn[((long)M * E) * nf],
+                                                 real(0.5) * tn[((long)(M + 1) * E) * nf], o);
 #pragma unroll
                     for (int v = 0; v < M; ++v) jump[v] += o[v];
                 } else {
@@ -1518,8 +1561,7 @@ static __global__ void __launch_bounds__(FINAL_BLOCK) k_dt_final(const Tables t,
 #pragma unroll
         for (int j = 0; j < 8; ++j) mx = fmax(mx, v[j]);
     }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) mx = fmax(mx, __shfl_xor(mx, m, 64));
+    mx = wave_max(mx);
     if ((tid & 63) == 0) red[tid >> 6] = mx;
     __syncthreads();
     if (tid == 0) {
@@ -1544,8 +1586,7 @@ static __global__ void __launch_bounds__(64) k_dt_slots(const Tables t, double *
         mx = fmax(mx, v[j]);
         slots[j * 64 + tid] = 0.0;
     }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) mx = fmax(mx, __shfl_xor(mx, m, 64));
+    mx = wave_max(mx);
     if (tid == 0) finish_dt(t, mx, is_mhd, dt);
 }
 
