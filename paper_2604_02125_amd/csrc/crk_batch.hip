@@ -46,10 +46,13 @@ struct BatchTile {
 // NDEG = 0: one launch over the whole work list, each tile taking the
 // degree-3 or degree-4 path by its problem's degree (the kernel then has the
 // degree-4 path's register budget for every tile).
+// (the degree-4 tiles' form of the flux, see lnmean_parts2)
+template <typename real, int FLUX>
+constexpr int batch_flux4() { return FLUX == VOL_RANOCHA && sizeof(real) == 8 ? (int)VOL_RANOCHA_DIRECT : FLUX; }
 template <typename real, int FLUX, int NDEG>
 struct BatchLocalLds {
     static constexpr int s3 = LocalShape<real, EQ_EULER, 2, 3, FLUX, false>::slots;
-    static constexpr int s4 = LocalShape<real, EQ_EULER, 2, 4, FLUX, false>::slots;
+    static constexpr int s4 = LocalShape<real, EQ_EULER, 2, 4, batch_flux4<real, FLUX>(), false>::slots;
     static constexpr int slots = NDEG == 3 ? s3 : (NDEG == 4 ? s4 : (s3 > s4 ? s3 : s4));
 };
 
@@ -67,7 +70,7 @@ __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(3))) k
         if (NDEG == 3 || (NDEG == 0 && bp.t.N == 3))
             local_tile<real, EQ_EULER, 2, 3, FLUX, 4, BLK, 1, false>(bp.t, bp.p[dir], tl.e0, smem, lane);
         else
-            local_tile<real, EQ_EULER, 2, 4, FLUX, 6, BLK, 2, false>(bp.t, bp.p[dir], tl.e0, smem, lane);
+            local_tile<real, EQ_EULER, 2, 4, batch_flux4<real, FLUX>(), 6, BLK, 2, false>(bp.t, bp.p[dir], tl.e0, smem, lane);
     };
     if constexpr (PERSIST) {
         for (int it = t0 + blockIdx.x; it < t1; it += gridDim.x) {

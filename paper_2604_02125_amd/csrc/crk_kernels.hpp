@@ -363,11 +363,20 @@ __device__ __forceinline__ void element_sync()
     }
 }
 
+// The volume flux's form in the local stages and the residual: FP64 Ranocha
+// at degrees 2 and 4 in 2D with the logarithms among the fields (measured at
+// lnmean_parts2).
+template <typename real, int EQ, int DIM, int N, int FLUX>
+struct VolumePhys {
+    static constexpr bool LOGS = FLUX == VOL_RANOCHA && sizeof(real) == 8 && DIM == 2 && (N == 2 || N == 4);
+    using type = typename PhysOf<real, EQ, DIM, (LOGS ? (int)VOL_RANOCHA_LOGS : FLUX)>::type;
+};
+
 // LDS slots (of BLK values each) used by the local-stage tile (BL: the
 // instance with the blending code)
 template <typename real, int EQ, int DIM, int N, int FLUX, bool BL = true>
 struct LocalShape {
-    using Phys = typename PhysOf<real, EQ, DIM, FLUX>::type;
+    using Phys = typename VolumePhys<real, EQ, DIM, N, FLUX>::type;
     static constexpr int n1 = N + 1;
     // the conservative two-point fluxes are symmetric for both systems (the
     // MHD non-conservative term is formed separately)
@@ -405,7 +414,7 @@ struct LocalShape {
                                  (N == 4 || (N == 3 && FLUX == VOL_RANOCHA));
     static constexpr bool DBF = DIM == 2 && N == 4 && !DTAB;
     static constexpr int DT = DTAB ? 1 : 0;
-    static constexpr int slots = (DBF ? 2 : 1) * Phys::NF + NX + ASL + CS + XB + DT;
+    static constexpr int slots = (DBF ? 2 : 1) * Phys::NL + NX + ASL + CS + XB + DT;
 };
 
 // One tile of BLK lanes: elements e0 .. e0 + BLK/(N+1)^DIM - 1 of one mesh.
@@ -419,7 +428,7 @@ template <typename real, int EQ, int DIM, int N, int FLUX, int S, int BLK, int T
           bool NCS = false>
 __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, long e0, real *smem, int lane = -1)
 {
-    using Phys = typename PhysOf<real, EQ, DIM, FLUX>::type;
+    using Phys = typename VolumePhys<real, EQ, DIM, N, FLUX>::type;
     using Shape = LocalShape<real, EQ, DIM, N, FLUX, BLEND>;
     constexpr int n1 = N + 1;
     constexpr int NP = DIM == 2 ? n1 * n1 : n1;
@@ -430,8 +439,8 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
     constexpr int NPRIM = Shape::NPRIM;
     constexpr int KSELF = Shape::KSELF;
     constexpr bool DBF = Shape::DBF;
-    real *lds0 = smem;                               // [NF][BLK] (two sets with DBF)
-    real *xch = smem + (DBF ? 2 : 1) * NF * BLK;     // [NX][BLK]
+    real *lds0 = smem;                               // [NL][BLK] (two sets with DBF)
+    real *xch = smem + (DBF ? 2 : 1) * Phys::NL * BLK;     // [NX][BLK]
     real *alds = xch + Shape::NX * BLK;   // [EPB][2 DIM + 1]
     real *clds = alds + Shape::ASL * BLK; // [CS][BLK]
     real *xb = clds + Shape::CS * BLK;    // [XB][BLK]
@@ -665,11 +674,11 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
         }
         real nd[NF];
         Phys::node(us, nd, ctx);
-        real *lds = lds0 + ((DBF && (i & 1)) ? NF * BLK : 0);
+        real *lds = lds0 + ((DBF && (i & 1)) ? Phys::NL * BLK : 0);
         if (i > 0 && !DBF) element_sync<NP, BLK>();    // the previous stage has finished reading LDS
 #pragma unroll
         for (int f = 0; f < NF; ++f)
-            if (Phys::paired(f)) lds[f * BLK + tid] = nd[f];
+            if (Phys::paired(f)) lds[Phys::lidx(f) * BLK + tid] = nd[f];
         element_sync<NP, BLK>();
         if (i == 0) {
             if (blend && valid) alpha = alds[le * NA];
@@ -718,7 +727,7 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
                 real ndq[NF];
 #pragma unroll
                 for (int f = 0; f < NF; ++f)
-                    if (Phys::paired(f)) ndq[f] = lds[f * BLK + base + q];
+                    if (Phys::paired(f)) ndq[f] = lds[Phys::lidx(f) * BLK + base + q];
                 real fs[M];
                 Phys::pair(d, nd, ndq, fs, ctx);
                 const real ck = dk(d, k);
@@ -773,8 +782,8 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
 #pragma unroll
                 for (int q = 0; q < n1; ++q) {
                     const int qq = line_node<N, DIM>(pd, d, q);
-                    gB += Dn[d][q] * lds[(5 + d) * BLK + base + qq];
-                    gpsi += Dn[d][q] * lds[8 * BLK + base + qq];
+                    gB += Dn[d][q] * lds[Phys::lidx(5 + d) * BLK + base + qq];
+                    gpsi += Dn[d][q] * lds[Phys::lidx(8) * BLK + base + qq];
                 }
                 real o[M];
                 MhdP<real, FLUX>::btimes(d, nd, gB, gpsi, o);
@@ -801,7 +810,7 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
                     const int q = line_node<N, DIM>(pd, d, qd);
                     real ndq[NF], fq[M], uq[M];
 #pragma unroll
-                    for (int f = 0; f < NF; ++f) ndq[f] = lds[f * BLK + base + q];
+                    for (int f = 0; f < NF; ++f) ndq[f] = lds[Phys::lidx(f) * BLK + base + q];
                     Phys::phys(d, ndq, fq, ctx);
                     Phys::cons(ndq, uq, ctx);
                     real lq;

@@ -18,6 +18,9 @@
 namespace crk {
 
 enum { VOL_CENTRAL = 0, VOL_KG = 1, VOL_RANOCHA = 2, VOL_DERIGS = 3 };
+// forms of the Ranocha flux inside the kernels: with the nodes' logarithms
+// among the fields (always so in FP32), or without at every degree
+enum { VOL_RANOCHA_LOGS = 4, VOL_RANOCHA_DIRECT = 5 };
 enum { EQ_EULER = 0, EQ_MHD = 1 };
 
 template <typename real>
@@ -122,17 +125,88 @@ __device__ __forceinline__ void lnmean_parts_fast(real x, real y, real lx, real 
     den = series ? poly : (ly - lx);
 }
 
+// In FP64 no logarithm is needed unless two states differ by almost a factor
+// of two: with u = ((x - y)/(x + y))^2 <= 0.09 (a ratio up to 1.857) the
+// denominator 2 artanh(sqrt u)/sqrt u is its Chebyshev interpolant of degree 9
+// in u (relative error below 1e-17), more accurate than the difference of two
+// rounded logarithms.  Beyond it (and for a NaN or a state that is not
+// positive, whose logarithm must be NaN) the quotient's logarithm is formed,
+// in a branch that a wavefront takes only if one of its pairs needs it.
+// Per node and stage that saves two logarithms and two fields to exchange.
+// us per step, logarithms per node / this (FP64): Ranocha n^2, degree 3, no
+// limiter 128 38.1/35.5, 256 98/88, 400 223/194; degree 1 256 34.9/32.1;
+// density wave of 64 elements 4.35/3.57; GLM-MHD degree 4 192^2 346/322.
+// Ranocha at degrees 2 and 4 keeps the logarithms: there (four pairs per node
+// at degree 4, three wavefronts per SIMD) the branches cost more than they
+// save (degree 4 256^2 235/257, with the limiter 253/304; degree 2 57/58),
+// except in the batch's degree-4 tiles (512 problems 10.22/9.91 ms per two
+// steps).
+// Tried against the branches: every pair first, far ones formed once more in
+// a loop behind (16 to 18 registers more, a wavefront fewer); both means of a
+// far pair in one looped copy of the code (30 registers more).
+constexpr double LNMEAN_UMAX = 0.09;
+__device__ __forceinline__ double lnmean_u(double x, double y)
+{
+    const double s = x + y, d = x - y;
+    return (d * d) * rcp_est1(s * fabs(s));
+}
+__device__ __forceinline__ bool lnmean_far(double u)   // u > UMAX, u < 0 or NaN
+{
+    return !(fabs(u - 0.5 * LNMEAN_UMAX) <= 0.5 * LNMEAN_UMAX);
+}
+__device__ __forceinline__ double lnmean_den(double u)
+{
+    double p = 0x1.4879d19ff0e3bp-3;
+    p = fma(p, u, 0x1.b33a9806b0725p-4);
+    p = fma(p, u, 0x1.13a1af0ce108dp-3);
+    p = fma(p, u, 0x1.3ae8be02f0137p-3);
+    p = fma(p, u, 0x1.745ed0db527fp-3);
+    p = fma(p, u, 0x1.c71c67084628ep-3);
+    p = fma(p, u, 0x1.24924937bc1ccp-2);
+    p = fma(p, u, 0x1.9999999976f83p-2);
+    p = fma(p, u, 0x1.5555555555617p-1);
+    return fma(p, u, 2.0);
+}
+// numerator and denominator of a mean of far states; the smaller state first,
+// so that both orders give the same bits
+__device__ __forceinline__ void lnmean_log(double x, double y, double &num, double &den)
+{
+    const double a = fmin(x, y), b = fmax(x, y);
+    num = b - a;
+    den = log_fp64(a > 0.0 ? b * rcp_nr(a) : -1.0);
+}
+// numerators and denominators of the two means of a pair, without logarithms
+// of the states
+__device__ __forceinline__ void lnmean_parts2(double x1, double y1, double x2, double y2, double &n1, double &d1,
+                                              double &n2, double &d2)
+{
+    const double u1 = lnmean_u(x1, y1), u2 = lnmean_u(x2, y2);
+    n1 = x1 + y1;
+    n2 = x2 + y2;
+    d1 = lnmean_den(u1);
+    d2 = lnmean_den(u2);
+    const bool far1 = lnmean_far(u1), far2 = lnmean_far(u2);
+    if (far1 || far2) {
+        if (far1) lnmean_log(x1, y1, n1, d1);
+        if (far2) lnmean_log(x2, y2, n2, d2);
+    }
+}
+
 // The two means an EC flux needs, ln-mean(x1, y1) and 1/ln-mean(x2, y2), with
 // one reciprocal: r = 1/(d1 n2), m1 = n1 n2 r = n1/d1, im2 = d2 d1 r = d2/n2.
 // Swapping the states flips the sign of n and d in the log branch and of
 // nothing in the series branch, so both results are symmetric bit for bit.
-template <typename real>
+template <bool LOGS, typename real>
 __device__ __forceinline__ void lnmean_pair(real x1, real y1, real lx1, real ly1, real x2, real y2, real lx2,
                                             real ly2, real &m1, real &im2)
 {
     real n1, d1, n2, d2;
-    lnmean_parts_fast(x1, y1, lx1, ly1, n1, d1);
-    lnmean_parts_fast(x2, y2, lx2, ly2, n2, d2);
+    if constexpr (!LOGS) {
+        lnmean_parts2(x1, y1, x2, y2, n1, d1, n2, d2);
+    } else {
+        lnmean_parts_fast(x1, y1, lx1, ly1, n1, d1);
+        lnmean_parts_fast(x2, y2, lx2, ly2, n2, d2);
+    }
     const real r = rcp_nr(d1 * n2);
     m1 = (n1 * n2) * r;
     im2 = (d2 * d1) * r;
@@ -144,15 +218,19 @@ __device__ __forceinline__ void lnmean_pair(real x1, real y1, real lx1, real ly1
 //   KG:      DIM+2 e = E/rho; all KG fields are stored halved, so that the
 //            arithmetic means of the flux are plain sums
 //   central: DIM+2 E
-//   Ranocha: DIM+2 ln rho, DIM+3 beta = rho/p, DIM+4 ln beta
+//   Ranocha: FP64 DIM+2 beta = rho/p; FP32 DIM+2 ln rho, DIM+3 beta, DIM+4 ln beta
 template <typename real, int DIM, int FLUX>
 struct EulerP {
     static constexpr int M = DIM + 2;
-    static constexpr int NF = (FLUX == VOL_RANOCHA) ? DIM + 5 : DIM + 3;
+    static constexpr bool RANOCHA = FLUX == VOL_RANOCHA || FLUX == VOL_RANOCHA_LOGS || FLUX == VOL_RANOCHA_DIRECT;
+    static constexpr bool LOGF = RANOCHA && (sizeof(real) == 4 || FLUX == VOL_RANOCHA_LOGS);   // logarithms among the fields
+    static constexpr int NF = LOGF ? DIM + 5 : DIM + 3;
+    static constexpr int LR = DIM + 2, BE = LOGF ? DIM + 3 : DIM + 2, LB = LOGF ? DIM + 4 : DIM + 2;
     static constexpr int P = DIM + 1;
     static constexpr bool HALF = (FLUX == VOL_KG);
     // every field is read by pair(), every variable has a pair flux
-    static constexpr int MX = M;
+    static constexpr int MX = M, NL = NF;
+    __device__ __forceinline__ static constexpr int lidx(int f) { return f; }
     __device__ __forceinline__ static constexpr bool paired(int) { return true; }
     __device__ __forceinline__ static constexpr bool pairs(int, int) { return true; }
     __device__ __forceinline__ static constexpr int xidx(int, int v) { return v; }
@@ -193,9 +271,11 @@ struct EulerP {
             nd[DIM + 2] = u[DIM + 1];
         } else if constexpr (LOGS) {
             const real beta = rho * rcp_nr(p);
-            nd[DIM + 2] = dlog(rho);
-            nd[DIM + 3] = beta;
-            nd[DIM + 4] = dlog(beta);
+            if constexpr (LOGF) {
+                nd[LR] = dlog(rho);
+                nd[LB] = dlog(beta);
+            }
+            nd[BE] = beta;
         }
     }
     __device__ __forceinline__ static void node(const real *u, real *nd, const Ctx<real> &c) { fields<true>(u, nd, c); }
@@ -288,8 +368,7 @@ struct EulerP {
             f[DIM + 1] = (rho * e + p) * vd;
         } else {
             real rho_ln, ibeta_ln;
-            lnmean_pair(a[0], b[0], a[DIM + 2], b[DIM + 2], a[DIM + 3], b[DIM + 3], a[DIM + 4], b[DIM + 4], rho_ln,
-                        ibeta_ln);
+            lnmean_pair<LOGF>(a[0], b[0], a[LR], b[LR], a[BE], b[BE], a[LB], b[LB], rho_ln, ibeta_ln);
             const real vd = real(0.5) * (a[1 + d] + b[1 + d]);
             real vv = real(0);
 #pragma unroll
@@ -308,10 +387,9 @@ struct EulerP {
     // a field, so that no register array is indexed at run time.
     __device__ __forceinline__ static void pair_rt(int d, const real *a, const real *b, real *f, const Ctx<real> &c)
     {
-        static_assert(FLUX == VOL_RANOCHA, "run-time direction: Ranocha flux only");
+        static_assert(RANOCHA, "run-time direction: Ranocha flux only");
         real rho_ln, ibeta_ln;
-        lnmean_pair(a[0], b[0], a[DIM + 2], b[DIM + 2], a[DIM + 3], b[DIM + 3], a[DIM + 4], b[DIM + 4], rho_ln,
-                    ibeta_ln);
+        lnmean_pair<LOGF>(a[0], b[0], a[LR], b[LR], a[BE], b[BE], a[LB], b[LB], rho_ln, ibeta_ln);
         real vk[DIM], vd = real(0), avd = real(0), bvd = real(0), vv = real(0);
 #pragma unroll
         for (int k = 0; k < DIM; ++k) {
@@ -335,8 +413,8 @@ struct EulerP {
 // ---------------------------------------------------------------- GLM-MHD
 // u = (rho, rho v (3), E, B (3), psi),
 // E = p/(gamma-1) + rho |v|^2/2 + |B|^2/2 + psi^2/2.
-// Fields: 0 rho, 1-3 v, 4 p, 5-7 B, 8 psi, 9 ln rho, 10 beta = rho/(2p),
-// 11 ln beta, 12 |v|^2, 13 |B|^2, 14 v.B
+// Fields: 0 rho, 1-3 v, 4 p, 5-7 B, 8 psi, 9 ln rho (FP32), 10 beta = rho/(2p),
+// 11 ln beta (FP32), 12 |v|^2, 13 |B|^2, 14 v.B
 template <typename real, int FLUX>
 struct MhdP {
     static constexpr int M = 9;
@@ -349,7 +427,13 @@ struct MhdP {
     // what it needs of |B|^2 itself)
     __device__ __forceinline__ static constexpr bool paired(int f)
     {
-        return !LEAN || (FLUX == VOL_CENTRAL ? (f < 9 || f > 11) : (f != 4 && f < 12));
+        return !LEAN || (FLUX == VOL_CENTRAL ? (f < 9 || f > 11) : (f < 4 || (f > 4 && f < 9) || f == 10));
+    }
+    // their number and place in the exchange
+    static constexpr int NL = !LEAN ? NF : (FLUX == VOL_CENTRAL ? 12 : 9);
+    __device__ __forceinline__ static constexpr int lidx(int f)
+    {
+        return !LEAN ? f : (FLUX == VOL_CENTRAL ? (f < 9 ? f : f - 3) : (f < 4 ? f : (f < 9 ? f - 1 : 8)));
     }
     // The fluxes of the normal field B_d and psi, c_h times an arithmetic
     // mean, need no pairs in a volume term: the rows of D sum to zero, so
@@ -370,7 +454,11 @@ struct MhdP {
         const real beta = real(0.5) * rho * rcp_nr(p);
         nd[0] = rho; nd[1] = v1; nd[2] = v2; nd[3] = v3; nd[4] = p;
         nd[5] = B1; nd[6] = B2; nd[7] = B3; nd[8] = psi;
-        nd[9] = dlog(rho); nd[10] = beta; nd[11] = dlog(beta);
+        nd[10] = beta;
+        if constexpr (!LEAN) {
+            nd[9] = dlog(rho);
+            nd[11] = dlog(beta);
+        }
         nd[12] = vv; nd[13] = BB; nd[14] = v1 * B1 + v2 * B2 + v3 * B3;
     }
 
@@ -449,8 +537,12 @@ struct MhdP {
         const real h = real(0.5);
         // both logarithmic means and 1/(2 mean beta) from one reciprocal
         real n1, d1, n2, d2;
-        lnmean_parts_fast(a[0], b[0], a[9], b[9], n1, d1);
-        lnmean_parts_fast(a[10], b[10], a[11], b[11], n2, d2);
+        if constexpr (LEAN) {
+            lnmean_parts2(a[0], b[0], a[10], b[10], n1, d1, n2, d2);
+        } else {
+            lnmean_parts_fast(a[0], b[0], a[9], b[9], n1, d1);
+            lnmean_parts_fast(a[10], b[10], a[11], b[11], n2, d2);
+        }
         const real tb = a[10] + b[10];
         const real dn = d1 * n2;
         const real r = rcp_nr(dn * tb);

@@ -45,7 +45,7 @@ template <typename real, int EQ, int DIM, int N, int FLUX, int BLK>
 __device__ __forceinline__ void rhs_lane(const Tables &t, const real *u, const Ctx<real> &ctx, int surface, int tid,
                                          int le, int node, long es, real *smem, real *R)
 {
-    using Phys = typename PhysOf<real, EQ, DIM, FLUX>::type;
+    using Phys = typename VolumePhys<real, EQ, DIM, N, FLUX>::type;
     using Shape = LocalShape<real, EQ, DIM, N, FLUX>;
     constexpr int n1 = N + 1;
     constexpr int NP = DIM == 2 ? n1 * n1 : n1;
@@ -80,7 +80,8 @@ __device__ __forceinline__ void rhs_lane(const Tables &t, const real *u, const C
     }
     Phys::node(uo, nd, ctx);
 #pragma unroll
-    for (int f = 0; f < NF; ++f) lds[f * BLK + tid] = nd[f];
+    for (int f = 0; f < NF; ++f)
+        if (Phys::paired(f)) lds[f * BLK + tid] = nd[f];
     element_sync<NP, BLK>();
 
 #pragma unroll
@@ -98,7 +99,8 @@ __device__ __forceinline__ void rhs_lane(const Tables &t, const real *u, const C
             const int q = line_node<N, DIM>(pd, d, qd);
             real ndq[NF], fs[M];
 #pragma unroll
-            for (int f = 0; f < NF; ++f) ndq[f] = lds[f * BLK + base + q];
+            for (int f = 0; f < NF; ++f)
+                if (Phys::paired(f)) ndq[f] = lds[f * BLK + base + q];
             Phys::pair(d, nd, ndq, fs, ctx);
             const real c = Tab<real>::dk(t, d, r, k);
 #pragma unroll

@@ -15,8 +15,7 @@
 //     residual that the other owns, and reads the mirrored fluxes of both
 //     directions for its own variables (the same number of LDS reads as both
 //     directions for all variables in half the lanes).
-//   - The stage state is put together from the two halves through LDS; of
-//     the node fields each lane evaluates one logarithm.
+//   - The stage state is put together from the two halves through LDS.
 // That is at most 256 registers, two wavefronts per SIMD, for three workgroup
 // barriers per stage.  Orszag-Tang 192^2, degree 4, FP64: local phase 345 ->
 // 300 us (372 -> 346 us per step against the one-lane kernel with the same
@@ -33,7 +32,7 @@ struct SplitShape {
     static constexpr int n1 = N + 1, NP = n1 * n1;
     static constexpr int HALF = tile_block<NP>();          // lanes per direction
     static constexpr int EPB = HALF / NP;
-    static constexpr int M = Phys::M, NF = Phys::NF;
+    static constexpr int M = Phys::M, NF = Phys::NF, NL = Phys::NL;
     static constexpr int OWN0 = 5;                          // variables of the x lane
     static constexpr bool SYM = N >= 2;
     static constexpr int NPRIM = SYM ? (n1 - 1) / 2 : 0;
@@ -46,7 +45,7 @@ struct SplitShape {
     static constexpr int X = 2 * NPRIM * MX;                // mirrored fluxes of both directions
     // fields, fluxes, handed-over values; u^n and the coefficients 2 D/dx
     // (in LDS instead of 34 registers)
-    static constexpr int slots = NF + X + M + M + 1;
+    static constexpr int slots = NL + X + M + M + 1;
     static_assert(Phys::LEAN, "written for the reduced exchange");
     static_assert(2 * n1 * n1 <= HALF, "the coefficient table fits one slot");
 };
@@ -64,8 +63,8 @@ __device__ __forceinline__ void split_lane(const Tables &t, const StepPtrs &a, l
     constexpr int d = ROLE;
     constexpr int V0 = ROLE == 0 ? 0 : Sh::OWN0, V1 = ROLE == 0 ? Sh::OWN0 : M, NV = V1 - V0;   // owned variables
     using FD = FaceData<EQ_MHD, M>;
-    real *lf = smem;                  // [NF][H] node fields
-    real *lx = lf + NF * H;           // [2][NPRIM][M][H] fluxes whose mirror a line neighbour takes
+    real *lf = smem;                  // [NL][H] node fields
+    real *lx = lf + Sh::NL * H;           // [2][NPRIM][M][H] fluxes whose mirror a line neighbour takes
     // [M][H] what a node's lanes hand each other: variable v of the residual
     // from the lane that does not own v, then of the stage state from the one
     // that does (each reads before it writes)
@@ -178,31 +177,14 @@ __device__ __forceinline__ void split_lane(const Tables &t, const StepPtrs &a, l
                 for (int v = 0; v < M; ++v) st[(((long)(face * S + i) * M + v) * E + e) * n1 + kk] = us[v];
             }
         }
-        // node fields; the logarithms one per lane
         real nd[NF];
-        Phys::node_basic(us, nd, ctx);
-        if constexpr (FLUX != VOL_CENTRAL) {
-            if constexpr (ROLE == 0) {
-                nd[9] = dlog(nd[0]);
-            } else {
-                nd[10] = real(0.5) * nd[0] * rcp_nr(nd[4]);
-                nd[11] = dlog(nd[10]);
-            }
-        }
+        Phys::node(us, nd, ctx);
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            const bool mine = ROLE == 0 ? (f < 5 || f == 9 || f >= 12) : (f >= 5 && f < 12 && f != 9);
-            if (mine && Phys::paired(f)) lf[f * H + lane] = nd[f];
+            const bool mine = ROLE == 0 ? (f < 5 || f >= 12) : (f >= 5 && f < 12);
+            if (mine && Phys::paired(f)) lf[Phys::lidx(f) * H + lane] = nd[f];
         }
         __syncthreads();
-        if constexpr (FLUX != VOL_CENTRAL) {
-            if constexpr (ROLE == 0) {
-                nd[10] = lf[10 * H + lane];
-                nd[11] = lf[11 * H + lane];
-            } else {
-                nd[9] = lf[9 * H + lane];
-            }
-        }
         // own direction: directly evaluated rotations, diagonal, non-conservative term
         real R[M];
 #pragma unroll
@@ -213,14 +195,14 @@ __device__ __forceinline__ void split_lane(const Tables &t, const StepPtrs &a, l
         for (int k = 1; k <= N; ++k) {
             const bool direct = !SYM || k <= NPRIM || k == KSELF;
             if (!direct) {
-                gB += Dk(k) * lf[(5 + d) * H + q[k]];
-                gpsi += Dk(k) * lf[8 * H + q[k]];
+                gB += Dk(k) * lf[Phys::lidx(5 + d) * H + q[k]];
+                gpsi += Dk(k) * lf[Phys::lidx(8) * H + q[k]];
                 continue;
             }
             real ndq[NF], fs[M];
 #pragma unroll
             for (int f = 0; f < NF; ++f)
-                if (Phys::paired(f)) ndq[f] = lf[f * H + q[k]];
+                if (Phys::paired(f)) ndq[f] = lf[Phys::lidx(f) * H + q[k]];
             Phys::pair(d, nd, ndq, fs, ctx);
 #pragma unroll
             for (int v = 0; v < M; ++v)
