@@ -645,28 +645,43 @@ crk_status crk_step(crk_solver *s, const void *u_in, void *u_out, double *dt_dev
 
 crk_status crk_prepare(crk_solver *s, const void *u, double *dt_dev, crk_stream stream)
 {
-    crk_status st = crk_compute_dt(s, u, dt_dev, stream);
+    crk_status st = need_ws(s);
     if (st) return st;
-    if (s->limiter == CRK_LIM_BLEND) st = crk_indicator(s, u, (double *)(s->ws + s->off_araw), nullptr, stream);
-    if (st) return st;
-    StepPtrs p{};
-    p.u_in = u; p.traces = s->ws + s->off_traces;
-    hipError_t e = dispatch(s, [&](auto fam) { return decltype(fam)::face_speed(s->t, s->flux, p, (hipStream_t)stream); });
-    // the wave-speed slots the interface phases merge into start at zero
-    // (a fill kernel, not a memset: safe inside a captured graph)
-    if (e == hipSuccess) e = launch_zero((double *)(s->ws + s->off_slots), DT_SLOTS, (hipStream_t)stream);
-    // tile flags of u (pipelined limiter with the modal indicator): both sets
-    // cleared, set 0 marked from the raw coefficients
+    if (!u || !dt_dev) return fail(CRK_ERR_ARG, "null pointer");
+    hipStream_t hs = (hipStream_t)stream;
+    const bool lim = s->limiter == CRK_LIM_BLEND, flags = use_tile_flags(s);
+    double *araw = (double *)(s->ws + s->off_araw), *slots = (double *)(s->ws + s->off_slots);
+    int *tiles = (int *)(s->ws + s->off_tiles);
     s->tparity = 0;
     s->tiles_valid = false;
-    if (e == hipSuccess && use_tile_flags(s)) {
-        int *tiles = (int *)(s->ws + s->off_tiles);
-        e = launch_zero_int(tiles, (int)(2 * s->ntiles), (hipStream_t)stream);
-        if (e == hipSuccess) {
+    hipError_t e = launch_zero(slots, DT_SLOTS, tiles, flags ? (int)(2 * s->ntiles) : 0, hs);
+    StepPtrs p{};
+    p.u_in = u; p.traces = s->ws + s->off_traces;
+    p.partials = slots;
+    p.dt_out = dt_dev;
+    p.alpha_raw_out = lim ? araw : nullptr;
+    p.features = (lim && s->mlp) ? (float *)(s->ws + s->off_features) : nullptr;
+    // tile flags of u: set 0, marked by the indicator; with a learned one, or
+    // walls, afterwards from the final coefficients and the mesh's neighbours
+    const bool after = s->mlp || s->t.wall[0] || s->t.wall[1];
+    p.tiles_out = flags && !after ? tiles : nullptr;
+    if (s->mesh.equation == CRK_GLM_MHD && s->prec == CRK_FP32) {
+        // dt by the reduction of crk_compute_dt, whose FP32 fast speeds the
+        // fused pass would round otherwise
+        st = crk_compute_dt(s, u, dt_dev, stream);
+        if (st) return st;
+        if (e == hipSuccess) e = dispatch(s, [&](auto fam) { return decltype(fam)::face_speed(s->t, s->flux, p, hs); });
+    } else if (e == hipSuccess) {
+        e = dispatch(s, [&](auto fam) { return decltype(fam)::state(s->t, s->flux, p, hs); });
+    }
+    if (e == hipSuccess && p.features)
+        e = launch_mlp_alpha(s->mlp, p.features, s->mlp_lo, s->mlp_hi, s->t.nelem, s->t.alpha_max, s->t.alpha_min, araw,
+                             nullptr, nullptr, hs);
+    if (e == hipSuccess && flags) {
+        if (after) {
             const long epb = tile_block_rt((int)s->t.nnode) / s->t.nnode;
             const dim3 g((unsigned)((s->t.nelem + BLOCK - 1) / BLOCK));
-            const double *araw = (const double *)(s->ws + s->off_araw);
-            hipLaunchKernelGGL(k_mark_tiles<2>, g, dim3(BLOCK), 0, (hipStream_t)stream, s->t, araw, (int)epb, tiles);
+            hipLaunchKernelGGL(k_mark_tiles<2>, g, dim3(BLOCK), 0, hs, s->t, (const double *)araw, (int)epb, tiles);
             e = hipGetLastError();
         }
         s->tiles_valid = e == hipSuccess;

@@ -10,6 +10,8 @@ template <typename real, int EQ, int DIM>
 struct Family {
     static hipError_t local(const Tables &t, int flux, const StepPtrs &p, hipStream_t s);
     static hipError_t interface(const Tables &t, int flux, const StepPtrs &p, hipStream_t s);
+    // dt, face wave speeds and raw indicator of p.u_in (crk_prepare)
+    static hipError_t state(const Tables &t, int flux, const StepPtrs &p, hipStream_t s);
     // wave speeds of the face nodes of p.u_in into the face data p.traces
     static hipError_t face_speed(const Tables &t, int flux, const StepPtrs &p, hipStream_t s);
     // nsteps pipelined steps of a one-dimensional mesh of at most RUN_BLOCK

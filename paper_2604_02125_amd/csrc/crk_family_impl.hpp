@@ -91,6 +91,12 @@ hipError_t Family<real, EQ, DIM>::face_speed(const Tables &t, int flux, const St
 }
 
 template <typename real, int EQ, int DIM>
+hipError_t Family<real, EQ, DIM>::state(const Tables &t, int flux, const StepPtrs &p, hipStream_t s)
+{
+    CRK_DEGREE_SWITCH(launch_state)
+}
+
+template <typename real, int EQ, int DIM>
 hipError_t Family<real, EQ, DIM>::run(const Tables &t, int flux, const StepPtrs &p, double *dt, int nsteps,
                                       hipStream_t s)
 {

@@ -1234,16 +1234,66 @@ __device__ __forceinline__ void block_max_lanes(double v, double *red, double *s
 // than one partial per workgroup.
 constexpr int DT_SLOTS = 256;
 
+// What a pipelined step needs of the state it starts from, with the state in
+// registers (one lane per node): CFL maximum, face wave speeds, raw indicator
+// (features, tile flags).  The tail of the interface phase, and crk_prepare.
+// MAXIMA: where the wave-speed maximum goes: MAX_TILE partials[slot], MAX_SLOTS
+// merged into partials[slot mod DT_SLOTS], MAX_WAVES one value per wavefront
+enum { MAX_TILE = 0, MAX_SLOTS = 1, MAX_WAVES = 2 };
+template <typename real, int EQ, int DIM, int N, int FLUX, int BLK, int MAXIMA>
+__device__ __forceinline__ void state_tail(const Tables &t, const StepPtrs &a, const real *u, int tid, int le, int node,
+                                           long e, bool valid, const Ctx<real> &ctx, long slot, double *dsmem)
+{
+    using Phys = typename PhysOf<real, EQ, DIM, FLUX>::type;
+    using FD = FaceData<EQ, Phys::M>;
+    constexpr int n1 = N + 1, M = Phys::M, NF = Phys::NF, nf = DIM == 2 ? n1 : 1;
+    const int pd[2] = {node % n1, DIM == 2 ? node / n1 : 0};
+    const long E = t.nelem;
+    real nd[NF];
+    Phys::node_basic(u, nd, ctx);
+    double sp = 0.0;
+    if (valid) {
+        real *ts = (real *)a.traces;
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) {
+            const real sd = face_speed<real, EQ, DIM, FLUX>(d, nd, ctx);
+            if constexpr (EQ == EQ_MHD) sp = fmax(sp, (double)sd);
+            else sp += (double)sd * t.invdx[d];
+            if (pd[d] == 0 || pd[d] == N) {
+                const int face = 2 * d + (pd[d] == N ? 1 : 0);
+                const int kk = DIM == 1 ? 0 : (d == 0 ? pd[1] : pd[0]);
+                ts[((long)(face * FD::NCT + FD::SPEED) * E + e) * nf + kk] = sd;
+            }
+        }
+    }
+    if constexpr (EQ == EQ_EULER) {
+        if (a.alpha_raw_out != nullptr) {
+            double ud[M];
+#pragma unroll
+            for (int v = 0; v < M; ++v) ud[v] = (double)u[v];
+            indicator_lanes<DIM, N, BLK>(t, tid, le, node, e, valid, indicator_eps<DIM>(ud, t.gamma), dsmem + BLK,
+                                         dsmem + 2 * BLK, a.alpha_raw_out, a.features, a.tiles_out);
+        }
+    }
+    if constexpr (MAXIMA == MAX_WAVES) {
+        sp = wave_max(sp);
+        if (tid % 64 == 0) a.partials[tid / 64] = sp;
+    } else if constexpr (MAXIMA == MAX_SLOTS) {
+        block_max_lanes<BLK, true>(sp, dsmem, a.partials + slot % DT_SLOTS);
+    } else {
+        block_max_lanes<BLK>(sp, dsmem, a.partials + slot);
+    }
+}
+
 // ---------------------------------------------------------------- K3: interface + final update
 // One lane per node; the face-node lanes apply the interface corrections.
 // u^n at the face nodes of both sides is read from the state the step
 // started from.  In the pipelined step every lane then holds u^{n+1} of its
 // node and the workgroup computes the CFL maximum and the raw indicator.
 // One tile of BLK lanes (elements e0 .. e0 + BLK/(N+1)^DIM - 1).  In the
-// pipelined step the tile's wave-speed maximum goes to partials[slot] (with
-// SLOTS: is merged into partials[slot mod DT_SLOTS]); dsmem holds 5 * BLK
-// doubles.
-template <typename real, int EQ, int DIM, int N, int FLUX, int BLK, bool SLOTS = false, bool NCS = false>
+// pipelined step the tile's wave-speed maximum goes where MAXIMA says; dsmem
+// holds 5 * BLK doubles.
+template <typename real, int EQ, int DIM, int N, int FLUX, int BLK, int MAXIMA = MAX_TILE, bool NCS = false>
 __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &a, long e0, long slot, double *dsmem)
 {
     using Phys = typename PhysOf<real, EQ, DIM, FLUX>::type;
@@ -1389,35 +1439,7 @@ __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &
     }
     if (!tail) return;
 
-    // pipelined tail: CFL maximum, face wave speeds and raw indicator of u^{n+1}
-    real nd[NF];
-    Phys::node_basic(u, nd, ctx);
-    double sp = 0.0;
-    if (valid) {
-        real *ts = (real *)a.traces;
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) {
-            const real sd = face_speed<real, EQ, DIM, FLUX>(d, nd, ctx);
-            if constexpr (EQ == EQ_MHD) sp = fmax(sp, (double)sd);
-            else sp += (double)sd * t.invdx[d];
-            if (pd[d] == 0 || pd[d] == N) {
-                const int face = 2 * d + (pd[d] == N ? 1 : 0);
-                const int kk = DIM == 1 ? 0 : (d == 0 ? pd[1] : pd[0]);
-                ts[((long)(face * FD::NCT + FD::SPEED) * E + e) * nf + kk] = sd;
-            }
-        }
-    }
-    if constexpr (EQ == EQ_EULER) {
-        if (a.alpha_raw_out != nullptr) {
-            double ud[M];
-#pragma unroll
-            for (int v = 0; v < M; ++v) ud[v] = (double)u[v];
-            indicator_lanes<DIM, N, BLK>(t, tid, le, node, e, valid, indicator_eps<DIM>(ud, t.gamma), dsmem + BLK,
-                                         dsmem + 2 * BLK, a.alpha_raw_out, a.features, a.tiles_out);
-        }
-    }
-    if constexpr (SLOTS) block_max_lanes<BLK, true>(sp, dsmem, a.partials + slot % DT_SLOTS);
-    else block_max_lanes<BLK>(sp, dsmem, a.partials + slot);
+    state_tail<real, EQ, DIM, N, FLUX, BLK, MAXIMA>(t, a, u, tid, le, node, e, valid, ctx, slot, dsmem);
 }
 
 template <typename real, int EQ, int DIM, int N, int FLUX, bool NCS = false>
@@ -1426,7 +1448,38 @@ __global__ void __launch_bounds__(tile_block<DIM == 2 ? (N + 1) * (N + 1) : N + 
     constexpr int NP = DIM == 2 ? (N + 1) * (N + 1) : N + 1;
     constexpr int TB = tile_block<NP>();
     __shared__ double dsmem[5 * TB];
-    interface_tile<real, EQ, DIM, N, FLUX, TB, true, NCS>(t, a, xcd_tile(blockIdx.x, gridDim.x) * (TB / NP), blockIdx.x, dsmem);
+    interface_tile<real, EQ, DIM, N, FLUX, TB, MAX_SLOTS, NCS>(t, a, xcd_tile(blockIdx.x, gridDim.x) * (TB / NP), blockIdx.x, dsmem);
+}
+
+// The same of a given state (crk_prepare): one pass over it, and three
+// launches, instead of one pass each for dt, the face wave speeds and the
+// indicator, in seven launches.  Bound by HBM on large meshes, by launch
+// latency on small ones: crk_prepare and ten steps of KHI 256^2 FP64 663 ->
+// 651 us, learned 512^2 1925 -> 1886, one training snapshot at 128^2 78 -> 61.
+template <typename real, int EQ, int DIM, int N, int FLUX>
+__global__ void __launch_bounds__(tile_block<DIM == 2 ? (N + 1) * (N + 1) : N + 1>()) k_state(const Tables t, const StepPtrs a)
+{
+    using Phys = typename PhysOf<real, EQ, DIM, FLUX>::type;
+    constexpr int NP = DIM == 2 ? (N + 1) * (N + 1) : N + 1, M = Phys::M;
+    constexpr int TB = tile_block<NP>();
+    __shared__ double dsmem[5 * TB];
+    const int tid = threadIdx.x;
+    int le = tid / NP;
+    const int node = tid - le * NP;
+    const long e = xcd_tile(blockIdx.x, gridDim.x) * (TB / NP) + le;
+    const bool valid = (le < TB / NP) && (e < t.nelem);
+    if (le >= TB / NP) le = 0;
+    const real *uo = (const real *)a.u_in;
+    real u[M];
+    if (valid) {
+#pragma unroll
+        for (int v = 0; v < M; ++v) u[v] = uo[((long)v * t.nelem + e) * NP + node];
+    } else {
+#pragma unroll
+        for (int v = 0; v < M; ++v) u[v] = real(v == 0 ? 1 : 0);
+    }
+    const Ctx<real> ctx = make_ctx<real>(t, nullptr);
+    state_tail<real, EQ, DIM, N, FLUX, TB, MAX_SLOTS>(t, a, u, tid, le, node, e, valid, ctx, blockIdx.x, dsmem);
 }
 
 // dt = cfl / ((N+1) m) from the global wave-speed maximum m (MHD: m = c_h and
@@ -1599,10 +1652,13 @@ static __global__ void __launch_bounds__(64) k_dt_slots(const Tables t, double *
     if (tid == 0) finish_dt(t, mx, is_mhd, dt);
 }
 
-static __global__ void k_zero(double *p, int n)
+// crk_prepare: the wave-speed slots and the tile flags start at zero (a fill
+// kernel, not a memset: safe inside a captured graph)
+static __global__ void __launch_bounds__(BLOCK) k_zero(double *p, int n, int *q, int m)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x * BLOCK + threadIdx.x;
     if (i < n) p[i] = 0.0;
+    if (i < m) q[i] = 0;
 }
 
 // tile flags of a state from its raw coefficients (flags zero on entry)
@@ -1612,12 +1668,6 @@ __global__ void __launch_bounds__(BLOCK) k_mark_tiles(const Tables t, const doub
     const long e = (long)blockIdx.x * BLOCK + threadIdx.x;
     if (e < t.nelem && alpha_raw[e] > 0.0) mark_tiles<DIM>(t, e, epb, tiles);
 }
-static __global__ void k_zero_int(int *p, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-
 // ---------------------------------------------------------------- K8: modal indicator
 template <typename real, int DIM, int N>
 __global__ void __launch_bounds__(BLOCK) k_indicator(const Tables t, const void *u_, double *alpha_raw, float *features)
@@ -1878,12 +1928,6 @@ hipError_t launch_local(const Tables &t, const StepPtrs &p, hipStream_t s)
     }
 }
 
-inline hipError_t launch_zero_int(int *p, int n, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_zero_int, dim3((n + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, p, n);
-    return hipGetLastError();
-}
-
 template <typename real, int EQ, int DIM, int N, int FLUX>
 hipError_t launch_interface(const Tables &t, const StepPtrs &p, hipStream_t s)
 {
@@ -1897,6 +1941,18 @@ hipError_t launch_interface(const Tables &t, const StepPtrs &p, hipStream_t s)
         hipLaunchKernelGGL((k_interface<real, EQ, DIM, N, FLUX>), dim3(grid), dim3(TB), 0, s, t, p);
     if (p.dt_out != nullptr)
         hipLaunchKernelGGL(k_dt_slots, dim3(1), dim3(64), 0, s, t, p.partials, EQ == EQ_MHD ? 1 : 0, p.dt_out);
+    return hipGetLastError();
+}
+
+// p.u_in: the state; the slots p.partials zero on entry (and on return)
+template <typename real, int EQ, int DIM, int N, int FLUX>
+hipError_t launch_state(const Tables &t, const StepPtrs &p, hipStream_t s)
+{
+    constexpr int NP = DIM == 2 ? (N + 1) * (N + 1) : N + 1;
+    constexpr int TB = tile_block<NP>();
+    constexpr int EPB = TB / NP;
+    hipLaunchKernelGGL((k_state<real, EQ, DIM, N, FLUX>), dim3((t.nelem + EPB - 1) / EPB), dim3(TB), 0, s, t, p);
+    hipLaunchKernelGGL(k_dt_slots, dim3(1), dim3(64), 0, s, t, p.partials, EQ == EQ_MHD ? 1 : 0, p.dt_out);
     return hipGetLastError();
 }
 
@@ -1947,9 +2003,9 @@ hipError_t launch_indicator(const Tables &t, const void *u, double *araw, double
     return hipGetLastError();
 }
 
-inline hipError_t launch_zero(double *p, int n, hipStream_t s)
+inline hipError_t launch_zero(double *p, int n, int *q, int m, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_zero, dim3((n + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, p, n);
+    hipLaunchKernelGGL(k_zero, dim3(((n > m ? n : m) + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, p, n, q, m);
     return hipGetLastError();
 }
 
