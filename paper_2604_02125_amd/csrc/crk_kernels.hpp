@@ -1508,7 +1508,8 @@ __device__ __forceinline__ void finish_dt(const Tables &t, double m, int is_mhd,
 // caller's buffers and the workspace before the first, written back after the
 // last.  Same device code and arithmetic as the separate launches.  64
 // elements of degree 3, Ranocha, FP64: 4.9 us per step, 5.2 with the phases
-// exchanging through global memory (4.3 with the shorter logarithm).
+// exchanging through global memory; 3.5 with the logarithmic means' series,
+// 3.4 with two barriers per step instead of five.
 constexpr int RUN_BLOCK = 256;   // one wavefront per SIMD: no register cap
 template <typename real, int EQ, int DIM, int N, int FLUX, int S, int TAB, bool BLEND>
 __global__ void __launch_bounds__(RUN_BLOCK) k_run(const Tables t, const StepPtrs a0, double *dt_io, int nsteps)
@@ -1520,7 +1521,8 @@ __global__ void __launch_bounds__(RUN_BLOCK) k_run(const Tables t, const StepPtr
     constexpr size_t LB = (size_t)LocalShape<real, EQ, DIM, N, FLUX, BLEND>::slots * RUN_BLOCK * sizeof(real);
     constexpr size_t DB = (size_t)5 * RUN_BLOCK * sizeof(double);
     __shared__ double pool[(LB > DB ? LB : DB) / sizeof(double)];   // local phase, then interface phase
-    __shared__ double dtl[2], smax;
+    constexpr int NW = RUN_BLOCK / 64;
+    __shared__ double dtl[NW][2], smax[NW];                  // dt: one copy per wavefront
     __shared__ real ub[2 * M * EMAX * NP];                  // the two state buffers
     __shared__ real trl[TR * EMAX];
     __shared__ double araw[BLEND ? EMAX : 1], asm_[BLEND ? EMAX : 1];
@@ -1532,13 +1534,14 @@ __global__ void __launch_bounds__(RUN_BLOCK) k_run(const Tables t, const StepPtr
     if constexpr (BLEND) {
         for (int i = tid; i < E; i += RUN_BLOCK) araw[i] = a0.alpha_raw[i];
     }
-    if (tid == 0) { dtl[0] = dt_io[0]; dtl[1] = dt_io[1]; }
+    double *dt = dtl[tid / 64];
+    if (tid % 64 == 0) { dt[0] = dt_io[0]; dt[1] = dt_io[1]; }
     __syncthreads();
     StepPtrs p{};
-    p.dt = dtl;
-    p.dt_out = dtl;                    // (non-null: the interface phase runs its tail)
+    p.dt = dt;
+    p.dt_out = dt;                     // (non-null: the interface phase runs its tail)
     p.traces = trl;
-    p.partials = &smax;
+    p.partials = smax;
     if constexpr (BLEND) {
         p.alpha_raw = araw;
         p.alpha_raw_out = araw;
@@ -1549,11 +1552,17 @@ __global__ void __launch_bounds__(RUN_BLOCK) k_run(const Tables t, const StepPtr
         p.u_out = ub + (k & 1 ? 0 : len);
         local_tile<real, EQ, DIM, N, FLUX, S, RUN_BLOCK, TAB, BLEND>(t, p, 0, (real *)pool);
         __syncthreads();
-        interface_tile<real, EQ, DIM, N, FLUX, RUN_BLOCK>(t, p, 0, 0, pool);
+        interface_tile<real, EQ, DIM, N, FLUX, RUN_BLOCK, MAX_WAVES>(t, p, 0, 0, pool);
         __syncthreads();
-        if (tid == 0) finish_dt(t, smax, EQ == EQ_MHD ? 1 : 0, dtl);
-        __syncthreads();
+        // every wavefront forms dt for itself (the next write of smax comes
+        // after the local phase's barrier)
+        double m = smax[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) m = fmax(m, smax[w]);
+        if (tid % 64 == 0) finish_dt(t, m, EQ == EQ_MHD ? 1 : 0, dt);
+        element_sync<64>();
     }
+    __syncthreads();
     for (int i = tid; i < len; i += RUN_BLOCK) {
         g0[i] = ub[i];
         g1[i] = ub[len + i];
@@ -1565,7 +1574,7 @@ __global__ void __launch_bounds__(RUN_BLOCK) k_run(const Tables t, const StepPtr
             a0.alpha_s[i] = asm_[i];
         }
     }
-    if (tid == 0) { dt_io[0] = dtl[0]; dt_io[1] = dtl[1]; }
+    if (tid == 0) { dt_io[0] = dt[0]; dt_io[1] = dt[1]; }
 }
 
 // ---------------------------------------------------------------- K1: time step
