@@ -261,8 +261,10 @@ __device__ __forceinline__ void mlp_tile_f32(const MlpF32 &w, const float *xs, m
 // touches lie on different banks).
 // Bound by the matrix cores' FP32 rate: 80 instructions of 32 cycles per 16
 // samples are 85 us for 1 310 720 samples on 1024 SIMDs at 2.4 GHz.  Measured
-// there: 151 us (161 without loading the next group ahead), against 405 us
-// for one lane per sample on the vector units with scalar weight loads.  The
+// there: 144 us (161 without loading the next group ahead and with the
+// parameters read two bytes at a time by each lane; 151 with those reads
+// alone: each block copies them to LDS first), against 405 us for one lane
+// per sample on the vector units with scalar weight loads.  The
 // three-part BF16 split of the indicator's tile takes 84 us but rounds
 // differently, and these outputs are FP32 sums that callers compare.
 constexpr int FW = 64, FROW = FW + 16;
@@ -275,11 +277,18 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const uint16_t *theta, cons
     const long wave = ((long)blockIdx.x * 256 + threadIdx.x) >> 6;
     const long nwaves = ((long)gridDim.x * 256) >> 6;
     const long ntiles = (n + FW - 1) / FW;
-    if (wave >= ntiles) return;                       // uniform per wavefront
-    const MlpView w = mlp_view(theta);
+    static_assert(sizeof(uint16_t) * NPAR <= sizeof(pool), "the parameters fit the rows");
+    uint16_t *th = (uint16_t *)pool[0];               // (before the rows take its place)
+    for (int i = threadIdx.x; i < NPAR; i += 256) th[i] = theta[i];
+    __syncthreads();
+    const MlpView w = mlp_view(th);
     float *h2 = pool[threadIdx.x >> 6];
     MlpF32 r;
     mlp_load_f32(w, col, kq, r);
+    const float b3 = bf2f(w.b3[0]);
+    const MlpView wg = mlp_view(theta);               // (W3: uniform, scalar loads)
+    __syncthreads();
+    if (wave >= ntiles) return;                       // uniform per wavefront
     // the lane's inputs of the group of 16 samples that starts at s0 (the
     // next group's are loaded ahead: a group's products hide one round trip)
     float nx[4];
@@ -305,9 +314,9 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const uint16_t *theta, cons
         }
         element_sync<64>();
         const long s = tile * FW + lane;
-        float z = bf2f(w.b3[0]);
+        float z = b3;
 #pragma unroll
-        for (int k = 0; k < HID; ++k) z = fmaf(bf2f(w.W3[k]), h2[k * FROW + lane], z);
+        for (int k = 0; k < HID; ++k) z = fmaf(bf2f(wg.W3[k]), h2[k * FROW + lane], z);
         if (s < n) {
             if (z_out) z_out[s] = z;
             if (alpha_out) alpha_out[s] = (double)alpha_max / (1.0 + exp(-(double)z));
