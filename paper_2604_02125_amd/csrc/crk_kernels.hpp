@@ -457,6 +457,7 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
     const long e = e0 + le;
     const bool valid = (le < EPB) && (e < t.nelem);
     if (le >= EPB) le = 0;                 // spare lanes read element 0's fields
+    const unsigned lo = valid ? (unsigned)tid : 0;   // within the tile's nodes
     const long es = valid ? e : 0;
     const int base = le * NP;
     const int pd[2] = {node % n1, DIM == 2 ? node / n1 : 0};
@@ -508,7 +509,7 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
     const real *uin = (const real *)a.u_in;
     real un[M];
 #pragma unroll
-    for (int v = 0; v < M; ++v) un[v] = uin[((long)v * E + es) * NP + node];
+    for (int v = 0; v < M; ++v) un[v] = (uin + ((long)v * E + e0) * NP)[lo];
 
     bool onface[DIM];
     int side[DIM];
@@ -922,7 +923,7 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
     }
     real *uout = (real *)a.u_out;
 #pragma unroll
-    for (int v = 0; v < M; ++v) uout[((long)v * E + e) * NP + node] = un[v] - rdt * W[v];
+    for (int v = 0; v < M; ++v) (uout + ((long)v * E + e0) * NP)[lo] = un[v] - rdt * W[v];
 }
 
 // With tile flags, the BLEND = false instance runs the clear tiles (and
@@ -945,7 +946,7 @@ k_local(const Tables t, const StepPtrs a)
     constexpr int SL = LocalShape<real, EQ, DIM, N, FLUX, BLEND>::slots * TB;
     static_assert(WPB == 1 || TB == 64, "several tiles per workgroup need single-wavefront tiles");
     __shared__ real smem[SL * WPB];
-    const int w = WPB == 1 ? 0 : (int)(threadIdx.x / 64);
+    const int w = WPB == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     const long tile = (long)xcd_chunk_tile(blockIdx.x, gridDim.x) * WPB + w;
     if constexpr (WPB > 1) {
         if (tile * (TB / NP) >= t.nelem) return;
@@ -972,7 +973,7 @@ k_local_any(const Tables t, const StepPtrs a)
     constexpr int SB = LocalShape<real, EQ_EULER, DIM, N, FLUX, true>::slots, SP = LocalShape<real, EQ_EULER, DIM, N, FLUX, false>::slots;
     constexpr int SL = (SB > SP ? SB : SP) * TB;
     __shared__ real smem[SL * WPB];
-    const int w = WPB == 1 ? 0 : (int)(threadIdx.x / 64);
+    const int w = WPB == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     const long tile = (long)xcd_chunk_tile(blockIdx.x, gridDim.x) * WPB + w;
     if (tile * (TB / NP) >= t.nelem) return;
     const int flagged = __builtin_amdgcn_readfirstlane(a.tiles_in[tile]);
@@ -1319,6 +1320,7 @@ __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &
     const real rdt = real(a.dt[0]);
     const real *tr = (const real *)a.traces;
     real *uo = (real *)a.u_out;
+    const unsigned lo = valid ? (unsigned)tid : 0;   // within the tile's nodes
 
     bool face_lane = false;
 #pragma unroll
@@ -1328,7 +1330,7 @@ __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &
     real u[M];
     if (face_lane || (tail && valid)) {
 #pragma unroll
-        for (int v = 0; v < M; ++v) u[v] = uo[((long)v * E + e) * NP + node];
+        for (int v = 0; v < M; ++v) u[v] = (uo + ((long)v * E + e0) * NP)[lo];
     } else {
 #pragma unroll
         for (int v = 0; v < M; ++v) u[v] = real(v == 0 ? 1 : 0);
@@ -1345,7 +1347,7 @@ __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &
             const real *uin = (const real *)a.u_in;
             real uno[M];
 #pragma unroll
-            for (int v = 0; v < M; ++v) uno[v] = uin[((long)v * E + e) * NP + node];
+            for (int v = 0; v < M; ++v) uno[v] = (uin + ((long)v * E + e0) * NP)[lo];
             Phys::node_basic(uno, ndo, ctx);
         }
         // both directions' shares are loaded before either is used: one round
@@ -1435,7 +1437,7 @@ __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &
     // writes); otherwise only the face nodes are written
     if (face_lane || (tail && valid)) {
 #pragma unroll
-        for (int v = 0; v < M; ++v) uo[((long)v * E + e) * NP + node] = u[v];
+        for (int v = 0; v < M; ++v) (uo + ((long)v * E + e0) * NP)[lo] = u[v];
     }
     if (!tail) return;
 
