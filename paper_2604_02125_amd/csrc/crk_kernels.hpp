@@ -238,6 +238,31 @@ __device__ __forceinline__ Nbrs neighbours(const Tables &t, long e)
     r.wall = (wx0 ? 1 : 0) | (wx1 ? 2 : 0) | (wy0 ? 4 : 0) | (wy1 ? 8 : 0);
     return r;
 }
+// The same for element e0 + le of the tile that starts at the (uniform)
+// element e0: the division by the row length is the tile's, on the scalar
+// unit, and the lanes form 32-bit sums instead of 64-bit products.  With the
+// selects of face_data_at, Euler: batch of 512 9583 -> 9413 us, 64-element 1D
+// runs (face data only) 690 -> 666; 256^2 and 1000 x 1024 meshes, which wait
+// for memory in these phases, the same within 0.2 %.
+template <int DIM, bool WALLS>
+__device__ __forceinline__ Nbrs neighbours_tile(const Tables &t, long e0, int le)
+{
+    if constexpr (DIM == 1) return neighbours<1, WALLS>(t, e0 + le);
+    Nbrs r;
+    const int nx = t.nx, E = t.nelem, f = (int)e0, ei = f + le;
+    const int ey0 = (int)(((unsigned long long)(unsigned)f * (unsigned long long)t.nx_m) >> t.nx_s);
+    int row = ey0 * nx, ex = f - row + le;
+    if (ex >= nx) { ex -= nx; row += nx; }
+    while (ex >= nx) { ex -= nx; row += nx; }      // (rows shorter than a tile)
+    const bool x0 = ex == 0, x1 = ex + 1 == nx, y0 = row == 0, y1 = row + nx == E;
+    const bool wx = WALLS && t.wall[0], wy = WALLS && t.wall[1];
+    r.n[0][0] = x0 ? (wx ? ei : ei + nx - 1) : ei - 1;
+    r.n[0][1] = x1 ? (wx ? ei : row) : ei + 1;
+    r.n[1][0] = y0 ? (wy ? ei : E - nx + ex) : ei - nx;
+    r.n[1][1] = y1 ? (wy ? ei : ex) : ei + nx;
+    r.wall = (wx && x0 ? 1 : 0) | (wx && x1 ? 2 : 0) | (wy && y0 ? 4 : 0) | (wy && y1 ? 8 : 0);
+    return r;
+}
 __device__ __forceinline__ Nbrs neighbours_any(const Tables &t, long e)
 {
     return t.dim == 1 ? neighbours<1>(t, e) : neighbours<2>(t, e);
@@ -275,6 +300,17 @@ struct FaceData {
     static constexpr int SPEED = NC;                       // component of the wave speed
     static constexpr int NCT = NC + 1;                     // components per face node
 };
+// first value of component c of face 2 d + side (nf values per element).
+// Euler: the lanes differ in a select of two uniform offsets, not in a product;
+// MHD, whose kernels hold more registers and hide the products: 1252 us with
+// the product, 1266 with the select (192^2 FP64, degree 4, four steps).
+template <int EQ, int M>
+__device__ __forceinline__ long face_data_at(long E, int nf, int d, int side, int c)
+{
+    using FD = FaceData<EQ, M>;
+    if constexpr (EQ == EQ_MHD) return (long)((2 * d + side) * FD::NCT + c) * E * nf;
+    return (long)(2 * d * FD::NCT + c) * E * nf + (side ? (long)FD::NCT * E * nf : 0);
+}
 
 template <typename real, int EQ, int DIM, int FLUX>
 __device__ __forceinline__ real face_speed(int d, const real *nd, const Ctx<real> &ctx)
@@ -529,21 +565,22 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
     Nbrs nb;
     auto face_speeds = [&](auto walls) {
         constexpr bool W = decltype(walls)::value;
-        nb = neighbours<DIM, W>(t, es);
+        if constexpr (EQ == EQ_MHD) nb = neighbours<DIM, W>(t, es);
+        else nb = neighbours_tile<DIM, W>(t, e0, valid ? le : 0);
         const real *ts = (const real *)a.traces;
         // every lane loads (an interior lane a face node of its own element,
         // a valid address whose value it drops), so that no branch waits
         // for the loads before the first stage needs them
 #pragma unroll
         for (int d = 0; d < DIM; ++d) {
-            const int face = 2 * d + side[d], nface = 2 * d + 1 - side[d];
+            const int face = 2 * d + side[d];
             const int kk = DIM == 1 ? 0 : (d == 0 ? pd[1] : pd[0]);
             // beyond a wall, the mirror image has the element's own wave speed
             const bool wl = W && ((nb.wall >> face) & 1);
             const long en = wl ? es : (side[d] ? nb.n[d][1] : nb.n[d][0]);
-            const int fn = wl ? face : nface;
-            const real so = ts[((long)(face * FD::NCT + FD::SPEED) * E + es) * nfn + kk];
-            const real sn = ts[((long)(fn * FD::NCT + FD::SPEED) * E + en) * nfn + kk];
+            const int sn_side = wl ? side[d] : 1 - side[d];
+            const real so = ts[face_data_at<EQ, M>(E, nfn, d, side[d], FD::SPEED) + es * nfn + kk];
+            const real sn = ts[face_data_at<EQ, M>(E, nfn, d, sn_side, FD::SPEED) + en * nfn + kk];
             real lam = dmax(so, sn);
             if constexpr (EQ == EQ_MHD) lam = dmax(lam, ctx.ch);
             lamd[d] = onface[d] ? lam : real(0);
@@ -911,9 +948,8 @@ __device__ __forceinline__ void local_tile(const Tables &t, const StepPtrs &a, l
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
         if (!onface[d]) continue;
-        const int face = 2 * d + side[d];
         const int kk = DIM == 1 ? 0 : (d == 0 ? pd[1] : pd[0]);
-        real *tb = tr + ((long)face * FD::NCT * E + e) * nfn + kk;
+        real *tb = tr + face_data_at<EQ, M>(E, nfn, d, side[d], 0) + e * nfn + kk;
 #pragma unroll
         for (int v = 0; v < M; ++v) tb[((long)v * E) * nfn] = P[d][v];
         if constexpr (EQ == EQ_MHD) {
@@ -1085,16 +1121,19 @@ __device__ __forceinline__ void indicator_lanes(const Tables &t, int tid, int le
     if constexpr (DPP) {
         // a(mk, j) = sum_i V[mk][i] eps(i, j): eps of the lane's node row by
         // quad broadcasts (lane 4 j + i holds eps(i, j))
-        double a = t.Vinv[mk][0] * dpp_double<0x00>(eps_node);
-        a += t.Vinv[mk][1] * dpp_double<0x55>(eps_node);
-        a += t.Vinv[mk][2] * dpp_double<0xAA>(eps_node);
-        a += t.Vinv[mk][3] * dpp_double<0xFF>(eps_node);
+        const double *V = &t.Vinv[0][0];
+        auto vk = [&](int c) { return V[(unsigned)(mk * (MAXN + 1) + c)]; };
+        auto vl = [&](int c) { return V[(unsigned)(ml * (MAXN + 1) + c)]; };
+        double a = vk(0) * dpp_double<0x00>(eps_node);
+        a += vk(1) * dpp_double<0x55>(eps_node);
+        a += vk(2) * dpp_double<0xAA>(eps_node);
+        a += vk(3) * dpp_double<0xFF>(eps_node);
         // m(mk, ml) = sum_j V[ml][j] a(mk, j): rotating the row right by
         // 4 s brings a(mk, (ml - s) mod 4) from lane 4 ((ml - s) mod 4) + mk
-        m = t.Vinv[ml][ml] * a;
-        m += t.Vinv[ml][(ml + 3) & 3] * dpp_double<0x124>(a);
-        m += t.Vinv[ml][(ml + 2) & 3] * dpp_double<0x128>(a);
-        m += t.Vinv[ml][(ml + 1) & 3] * dpp_double<0x12C>(a);
+        m = vl(ml) * a;
+        m += vl((ml + 3) & 3) * dpp_double<0x124>(a);
+        m += vl((ml + 2) & 3) * dpp_double<0x128>(a);
+        m += vl((ml + 1) & 3) * dpp_double<0x12C>(a);
     } else {
         eps[tid] = eps_node;
         element_sync<NP, BLK>();
@@ -1261,9 +1300,8 @@ __device__ __forceinline__ void state_tail(const Tables &t, const StepPtrs &a, c
             if constexpr (EQ == EQ_MHD) sp = fmax(sp, (double)sd);
             else sp += (double)sd * t.invdx[d];
             if (pd[d] == 0 || pd[d] == N) {
-                const int face = 2 * d + (pd[d] == N ? 1 : 0);
                 const int kk = DIM == 1 ? 0 : (d == 0 ? pd[1] : pd[0]);
-                ts[((long)(face * FD::NCT + FD::SPEED) * E + e) * nf + kk] = sd;
+                ts[face_data_at<EQ, M>(E, nf, d, pd[d] == N ? 1 : 0, FD::SPEED) + e * nf + kk] = sd;
             }
         }
     }
@@ -1341,7 +1379,9 @@ __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &
         // the neighbour's share of the interface flux (the own share and the
         // own trace term were applied by the local phase), lifted with
         // dg_R/dxi = delta_pN/w_N, dg_L/dxi = -delta_p0/w_0
-        const Nbrs nb = neighbours<DIM, W>(t, e);
+        Nbrs nb;
+        if constexpr (EQ == EQ_MHD) nb = neighbours<DIM, W>(t, e);
+        else nb = neighbours_tile<DIM, W>(t, e0, le);
         real ndo[NF];
         if constexpr (EQ == EQ_MHD) {
             const real *uin = (const real *)a.u_in;
@@ -1363,11 +1403,9 @@ __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &
             if (!(pd[d] == 0 || pd[d] == N)) continue;
             const int side = pd[d] == N ? 1 : 0;
             const long en = side ? nb.n[d][1] : nb.n[d][0];
-            const int nface = 2 * d + 1 - side;
             const int kk = DIM == 1 ? 0 : (d == 0 ? pd[1] : pd[0]);
             const bool wl = W && ((nb.wall >> (2 * d + side)) & 1);
-            const real *tn = wl ? tr + ((long)(2 * d + side) * FD::NCT * E + e) * nf + kk
-                                : tr + ((long)nface * FD::NCT * E + en) * nf + kk;
+            const real *tn = tr + face_data_at<EQ, M>(E, nf, d, wl ? side : 1 - side, 0) + (wl ? e : en) * nf + kk;
 #pragma unroll
             for (int v = 0; v < NL; ++v) share[d][v] = tn[((long)v * E) * nf];
         }
@@ -1383,8 +1421,7 @@ __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &
             // element's own P: f_d(R u) = -R f_d(u) for every state, so both
             // the time averages and the first-order part mirror that way.
             const bool wl = W && ((nb.wall >> (2 * d + side)) & 1);
-            const real *tn = wl ? tr + ((long)(2 * d + side) * FD::NCT * E + e) * nf + kk
-                                : tr + ((long)nface * FD::NCT * E + en) * nf + kk;
+            const real *tn = tr + face_data_at<EQ, M>(E, nf, d, wl ? side : 1 - side, 0) + (wl ? e : en) * nf + kk;
             real jump[M];
 #pragma unroll
             for (int v = 0; v < M; ++v) {
