@@ -1280,7 +1280,7 @@ constexpr int DT_SLOTS = 256;
 // MAXIMA: where the wave-speed maximum goes: MAX_TILE partials[slot], MAX_SLOTS
 // merged into partials[slot mod DT_SLOTS], MAX_WAVES one value per wavefront
 enum { MAX_TILE = 0, MAX_SLOTS = 1, MAX_WAVES = 2 };
-template <typename real, int EQ, int DIM, int N, int FLUX, int BLK, int MAXIMA>
+template <typename real, int EQ, int DIM, int N, int FLUX, int BLK, int MAXIMA, int WPB = 1>
 __device__ __forceinline__ void state_tail(const Tables &t, const StepPtrs &a, const real *u, int tid, int le, int node,
                                            long e, bool valid, const Ctx<real> &ctx, long slot, double *dsmem)
 {
@@ -1318,7 +1318,23 @@ __device__ __forceinline__ void state_tail(const Tables &t, const StepPtrs &a, c
         sp = wave_max(sp);
         if (tid % 64 == 0) a.partials[tid / 64] = sp;
     } else if constexpr (MAXIMA == MAX_SLOTS) {
-        block_max_lanes<BLK, true>(sp, dsmem, a.partials + slot % DT_SLOTS);
+        if constexpr (WPB == 1) {
+            block_max_lanes<BLK, true>(sp, dsmem, a.partials + slot % DT_SLOTS);
+        } else {
+            static_assert(BLK == 64, "a wavefront per tile");
+            // (the workgroup's wavefronts' tiles: spare ones, without elements, give zero)
+            __shared__ double wm[WPB];
+            sp = wave_max(sp);
+            if (tid == 0) wm[threadIdx.x / 64] = sp;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                double r = wm[0];
+#pragma unroll
+                for (int w = 1; w < WPB; ++w) r = fmax(r, wm[w]);
+                const double rr = r >= 0.0 ? r : 0.0;
+                atomicMax((unsigned long long *)(a.partials + slot % DT_SLOTS), (unsigned long long)__double_as_longlong(rr));
+            }
+        }
     } else {
         block_max_lanes<BLK>(sp, dsmem, a.partials + slot);
     }
@@ -1332,7 +1348,7 @@ __device__ __forceinline__ void state_tail(const Tables &t, const StepPtrs &a, c
 // One tile of BLK lanes (elements e0 .. e0 + BLK/(N+1)^DIM - 1).  In the
 // pipelined step the tile's wave-speed maximum goes where MAXIMA says; dsmem
 // holds 5 * BLK doubles.
-template <typename real, int EQ, int DIM, int N, int FLUX, int BLK, int MAXIMA = MAX_TILE, bool NCS = false>
+template <typename real, int EQ, int DIM, int N, int FLUX, int BLK, int MAXIMA = MAX_TILE, bool NCS = false, int WPB = 1>
 __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &a, long e0, long slot, double *dsmem)
 {
     using Phys = typename PhysOf<real, EQ, DIM, FLUX>::type;
@@ -1341,7 +1357,7 @@ __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &
     constexpr int EPB = BLK / NP;
     constexpr int M = Phys::M;
     constexpr int NF = Phys::NF;
-    const int tid = threadIdx.x;
+    const int tid = WPB == 1 ? threadIdx.x : threadIdx.x % 64;
     int le = tid / NP;
     const int node = tid - le * NP;
     const long e = e0 + le;
@@ -1478,16 +1494,18 @@ __device__ __forceinline__ void interface_tile(const Tables &t, const StepPtrs &
     }
     if (!tail) return;
 
-    state_tail<real, EQ, DIM, N, FLUX, BLK, MAXIMA>(t, a, u, tid, le, node, e, valid, ctx, slot, dsmem);
+    state_tail<real, EQ, DIM, N, FLUX, BLK, MAXIMA, WPB>(t, a, u, tid, le, node, e, valid, ctx, slot, dsmem);
 }
 
-template <typename real, int EQ, int DIM, int N, int FLUX, bool NCS = false>
-__global__ void __launch_bounds__(tile_block<DIM == 2 ? (N + 1) * (N + 1) : N + 1>()) k_interface(const Tables t, const StepPtrs a)
+template <typename real, int EQ, int DIM, int N, int FLUX, bool NCS = false, int WPB = 1>
+__global__ void __launch_bounds__(tile_block<DIM == 2 ? (N + 1) * (N + 1) : N + 1>() * WPB) k_interface(const Tables t, const StepPtrs a)
 {
     constexpr int NP = DIM == 2 ? (N + 1) * (N + 1) : N + 1;
     constexpr int TB = tile_block<NP>();
-    __shared__ double dsmem[5 * TB];
-    interface_tile<real, EQ, DIM, N, FLUX, TB, MAX_SLOTS, NCS>(t, a, xcd_tile(blockIdx.x, gridDim.x) * (TB / NP), blockIdx.x, dsmem);
+    __shared__ double dsmem[5 * TB * WPB];
+    const int w = WPB == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+    interface_tile<real, EQ, DIM, N, FLUX, TB, MAX_SLOTS, NCS, WPB>(t, a, (xcd_tile(blockIdx.x, gridDim.x) * WPB + w) * (TB / NP),
+                                                                    blockIdx.x, dsmem + 5 * TB * w);
 }
 
 // The same of a given state (crk_prepare): one pass over it, and three
@@ -1495,17 +1513,18 @@ __global__ void __launch_bounds__(tile_block<DIM == 2 ? (N + 1) * (N + 1) : N + 
 // indicator, in seven launches.  Bound by HBM on large meshes, by launch
 // latency on small ones: crk_prepare and ten steps of KHI 256^2 FP64 663 ->
 // 651 us, learned 512^2 1925 -> 1886, one training snapshot at 128^2 78 -> 61.
-template <typename real, int EQ, int DIM, int N, int FLUX>
-__global__ void __launch_bounds__(tile_block<DIM == 2 ? (N + 1) * (N + 1) : N + 1>()) k_state(const Tables t, const StepPtrs a)
+template <typename real, int EQ, int DIM, int N, int FLUX, int WPB = 1>
+__global__ void __launch_bounds__(tile_block<DIM == 2 ? (N + 1) * (N + 1) : N + 1>() * WPB) k_state(const Tables t, const StepPtrs a)
 {
     using Phys = typename PhysOf<real, EQ, DIM, FLUX>::type;
     constexpr int NP = DIM == 2 ? (N + 1) * (N + 1) : N + 1, M = Phys::M;
     constexpr int TB = tile_block<NP>();
-    __shared__ double dsmem[5 * TB];
-    const int tid = threadIdx.x;
+    __shared__ double dsmem[5 * TB * WPB];
+    const int tid = WPB == 1 ? threadIdx.x : threadIdx.x % 64;
+    const int w = WPB == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     int le = tid / NP;
     const int node = tid - le * NP;
-    const long e = xcd_tile(blockIdx.x, gridDim.x) * (TB / NP) + le;
+    const long e = (xcd_tile(blockIdx.x, gridDim.x) * WPB + w) * (TB / NP) + le;
     const bool valid = (le < TB / NP) && (e < t.nelem);
     if (le >= TB / NP) le = 0;
     const real *uo = (const real *)a.u_in;
@@ -1518,7 +1537,7 @@ __global__ void __launch_bounds__(tile_block<DIM == 2 ? (N + 1) * (N + 1) : N + 
         for (int v = 0; v < M; ++v) u[v] = real(v == 0 ? 1 : 0);
     }
     const Ctx<real> ctx = make_ctx<real>(t, nullptr);
-    state_tail<real, EQ, DIM, N, FLUX, TB, MAX_SLOTS>(t, a, u, tid, le, node, e, valid, ctx, blockIdx.x, dsmem);
+    state_tail<real, EQ, DIM, N, FLUX, TB, MAX_SLOTS, WPB>(t, a, u, tid, le, node, e, valid, ctx, blockIdx.x, dsmem + 5 * TB * w);
 }
 
 // dt = cfl / ((N+1) m) from the global wave-speed maximum m (MHD: m = c_h and
@@ -1993,10 +2012,17 @@ hipError_t launch_interface(const Tables &t, const StepPtrs &p, hipStream_t s)
     constexpr int TB = tile_block<NP>();
     constexpr int EPB = TB / NP;
     const int grid = (t.nelem + EPB - 1) / EPB;
+    // Four one-wavefront tiles per workgroup, whose maxima join in LDS before
+    // the atomic merge: a quarter of the merges and of the workgroups.  One /
+    // four per workgroup (Euler: together with the uniform addresses above,
+    // which alone change nothing here): KHI 256^2 FP64 643 / 627 us, KHI
+    // 1000 x 1024 FP32 4326 / 4264, MHD 121 x 90 FP32 197.6 / 194.8; 768 tiles
+    // (32 x 96 elements) the same.  Larger tiles join two wavefronts already.
+    constexpr int WPB = TB == 64 ? 4 : 1;
     if (EQ == EQ_MHD && p.stage_tr != nullptr)
         hipLaunchKernelGGL((k_interface<real, EQ, DIM, N, FLUX, true>), dim3(grid), dim3(TB), 0, s, t, p);
     else
-        hipLaunchKernelGGL((k_interface<real, EQ, DIM, N, FLUX>), dim3(grid), dim3(TB), 0, s, t, p);
+        hipLaunchKernelGGL((k_interface<real, EQ, DIM, N, FLUX, false, WPB>), dim3((grid + WPB - 1) / WPB), dim3(TB * WPB), 0, s, t, p);
     if (p.dt_out != nullptr)
         hipLaunchKernelGGL(k_dt_slots, dim3(1), dim3(64), 0, s, t, p.partials, EQ == EQ_MHD ? 1 : 0, p.dt_out);
     return hipGetLastError();
@@ -2009,7 +2035,9 @@ hipError_t launch_state(const Tables &t, const StepPtrs &p, hipStream_t s)
     constexpr int NP = DIM == 2 ? (N + 1) * (N + 1) : N + 1;
     constexpr int TB = tile_block<NP>();
     constexpr int EPB = TB / NP;
-    hipLaunchKernelGGL((k_state<real, EQ, DIM, N, FLUX>), dim3((t.nelem + EPB - 1) / EPB), dim3(TB), 0, s, t, p);
+    constexpr int WPB = TB == 64 ? 4 : 1;   // (as launch_interface)
+    const int grid = ((t.nelem + EPB - 1) / EPB + WPB - 1) / WPB;
+    hipLaunchKernelGGL((k_state<real, EQ, DIM, N, FLUX, WPB>), dim3(grid), dim3(TB * WPB), 0, s, t, p);
     hipLaunchKernelGGL(k_dt_slots, dim3(1), dim3(64), 0, s, t, p.partials, EQ == EQ_MHD ? 1 : 0, p.dt_out);
     return hipGetLastError();
 }
