@@ -261,11 +261,12 @@ crk_status crk_step(crk_solver *s, const void *u_in, void *u_out, double *dt_dev
  * again (CRK_ERR_STATE). */
 #define CRK_PHASE_LOCAL 1
 #define CRK_PHASE_INTERFACE 2
-/* The local phase in its two launches, for timing each on its own: the
- * element tiles where no blending coefficient can be positive run a kernel
- * instance without the blending code (PLAIN), the others the instance with
- * it (BLEND).  CRK_PHASE_LOCAL = both; issued separately, PLAIN comes first
- * and both come before the interface phase. */
+/* The two halves of the local phase, for timing each on its own: the
+ * element tiles where no blending coefficient can be positive run the code
+ * without blending (PLAIN), the others the code with it (BLEND).
+ * CRK_PHASE_LOCAL = both; issued separately, PLAIN comes first and both come
+ * before the interface phase.  Where one launch serves both kinds of tile
+ * (small meshes, costly fluxes) PLAIN issues it and BLEND does nothing. */
 #define CRK_PHASE_LOCAL_PLAIN 4
 #define CRK_PHASE_LOCAL_BLEND 8
 crk_status crk_prepare(crk_solver *s, const void *u, double *dt_dev, crk_stream stream);

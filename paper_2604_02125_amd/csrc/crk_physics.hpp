@@ -4,7 +4,8 @@
 //   - M: number of conserved variables;
 //   - NF: number of per-node fields staged in LDS for the two-point fluxes
 //     (primitive variables plus whatever a flux needs per node, such as the
-//     logarithms used by the logarithmic means);
+//     logarithms used by the logarithmic means, where a flux takes them per
+//     node: FP32, and the Ranocha forms named below);
 //   - node():  fields from the conserved state;
 //   - pair():  symmetric two-point flux f_S,d(u_a, u_b)  (eq:entropy.cons.flux.dev);
 //   - phys():  physical flux f_d(u);

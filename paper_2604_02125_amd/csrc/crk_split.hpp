@@ -17,10 +17,11 @@
 //     directions for all variables in half the lanes).
 //   - The stage state is put together from the two halves through LDS.
 // That is at most 256 registers, two wavefronts per SIMD, for three workgroup
-// barriers per stage.  Orszag-Tang 192^2, degree 4, FP64: local phase 345 ->
-// 300 us (372 -> 346 us per step against the one-lane kernel with the same
-// pair flux and logarithm).  Bound by vector issue (62 % busy) and LDS
-// (53 %) together; what is left of the difference is waiting at barriers.
+// barriers per stage.  Orszag-Tang 192^2, degree 4, FP64, when written: local
+// phase 345 -> 300 us (372 -> 346 us per step against the one-lane kernel
+// with the same pair flux and logarithm), bound by vector issue (62 % busy)
+// and LDS (53 %) together, the rest waiting at barriers.  With the series for
+// the logarithmic means the phase takes 262 to 288 us, the step 312.
 #pragma once
 #include "crk_kernels.hpp"
 
