@@ -1567,7 +1567,8 @@ __device__ __forceinline__ void finish_dt(const Tables &t, double m, int is_mhd,
 // last.  Same device code and arithmetic as the separate launches.  64
 // elements of degree 3, Ranocha, FP64: 4.9 us per step, 5.2 with the phases
 // exchanging through global memory; 3.5 with the logarithmic means' series,
-// 3.4 with two barriers per step instead of five.
+// 3.4 with two barriers per step instead of five, 3.3 without 64-bit products
+// in the addresses.
 constexpr int RUN_BLOCK = 256;   // one wavefront per SIMD: no register cap
 template <typename real, int EQ, int DIM, int N, int FLUX, int S, int TAB, bool BLEND>
 __global__ void __launch_bounds__(RUN_BLOCK) k_run(const Tables t, const StepPtrs a0, double *dt_io, int nsteps)
