@@ -602,10 +602,13 @@ __global__ void __launch_bounds__(256) k_mlp_alpha(const uint16_t *theta, const 
             x[i] = ev ? features[e * NIN + 4 * kq + i] : 0.f;
             inside &= (x[i] >= flo[i]) && (x[i] <= fhi[i]);
         }
-        // the four lanes of an element (col, col + 16, col + 32, col + 48)
-        inside = inside && __shfl_xor((int)inside, 16) && __shfl_xor((int)inside, 32);
+        // all four lanes of an element (col, col + 16, col + 32, col + 48);
+        // every lane takes part in both exchanges, whatever its own four say
+        int in = inside ? 1 : 0;
+        in &= __shfl_xor(in, 16);
+        in &= __shfl_xor(in, 32);
         const float z = mlp_tile(w, x);
-        if (kq == 0 && ev && inside && isfinite(z)) {
+        if (kq == 0 && ev && in && isfinite(z)) {
             double a = alpha_max / (1.0 + exp(-(double)z));
             if (a < alpha_min) a = 0.0;
             alpha_raw[e] = a;
