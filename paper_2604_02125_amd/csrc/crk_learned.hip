@@ -52,11 +52,11 @@ __device__ __forceinline__ MlpView mlp_view(const uint16_t *th)
 }
 
 // ---------------------------------------------------------------- the network on the matrix cores
-// Every layer is formed transposed, Y^T = W X^T, for 16 samples at a time:
-// the BF16 weights are the exact A operand, and every FP32 activation enters
-// the B operand as the sum of three BF16 parts (x = hi + mid + lo to within
-// 2^-26 |x|), so each product is exact in FP32 and the result is the FP32
-// network up to the summation order.  The first layer (16 inputs) uses
+// Every layer is formed transposed, Y^T = W X^T, for 16 samples at a time.
+// In the indicator's tile (mlp_tile) the BF16 weights are the exact A operand,
+// and every FP32 activation enters the B operand as the sum of three BF16
+// parts (x = hi + mid + lo to within 2^-26 |x|), so each product is exact in
+// FP32 and the result is the FP32 network up to the summation order.  The first layer (16 inputs) uses
 // v_mfma_f32_16x16x16_bf16, operand layout (lane l, i = 0..3):
 // A[l % 16][4 (l / 16) + i], B[4 (l / 16) + i][l % 16],
 // D[4 (l / 16) + i][l % 16]; a layer's D is therefore already a B operand of
@@ -101,10 +101,10 @@ __device__ __forceinline__ void split3v(const float *x, int n, V &h, V &m, V &l)
 // K = 32 form, reinterpreted as a whole vector (built element by element
 // from bit-cast BF16 values, the operand reached the instruction wrongly
 // packed with this compiler, although its bits read back unchanged)
-__device__ __forceinline__ mx_b8 as_b8(const mx_s8 &t) { return __builtin_bit_cast(mx_b8, t); }
 __device__ __forceinline__ mx_b8 join8(const mx_s4 &p, const mx_s4 &q)
 {
-    return as_b8(__builtin_shufflevector(p, q, 0, 1, 2, 3, 4, 5, 6, 7));
+    const mx_s8 t = __builtin_shufflevector(p, q, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(mx_b8, t);
 }
 
 // acc + a (bh + bm + bl), the small parts first
@@ -120,17 +120,6 @@ __device__ __forceinline__ mx_f4 mfma3k32(const mx_b8 &a, const mx_b8 &bh, const
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bm, acc, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bh, acc, 0, 0, 0);
 }
-// acc + (ah + am + al)(bh + bm + bl) without the three products below 2^-26
-__device__ __forceinline__ mx_f4 mfma6k32(const mx_b8 *a, const mx_b8 *b, mx_f4 acc)
-{
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[2], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2], b[0], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[1], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[1], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[0], acc, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0], acc, 0, 0, 0);
-}
-
 constexpr int MX_TILE = 16;
 constexpr unsigned MLP_GRID = 2 * 256;   // workgroups of the inference kernels: two wavefronts per SIMD of 256 CUs
 static_assert(NIN == 16 && HID == 64, "the tiling below is written for 16 inputs and 64 hidden units");
@@ -326,44 +315,38 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const uint16_t *theta, cons
 }
 
 // Gradient of the mean binary cross-entropy of sigmoid(z) against y over n
-// samples.  A workgroup takes 64 samples at a time, 16 per wavefront: the
-// forward tile in FP32 (in index order, so that no ReLU at the edge of
-// rounding switches sides) and the back-propagated sums D1^T = W2^T D2^T as in
-// the indicator's layers.  The weight gradients gW2 = D2 H1^T and
-// gW1 = D1 X^T are products with the 64 samples as the contraction, wavefront
-// w taking the rows 16 w ..: there a lane needs eight samples of one hidden
-// unit where the layers leave four units of one sample, so D2, H1, D1, X (and
-// E = dz relu(a2), whose row sums are gW3) pass through LDS in FP32 (rows of
-// GROW values: 16-byte aligned, rows four apart on different banks).  Both
-// operands are split in three BF16 parts, six products each.  The gradient
-// stays in registers over all of a workgroup's samples, which leaves one
-// partial gradient.
+// samples, in FP32 throughout (v_mfma_f32_16x16x4_f32: fused multiply-adds of
+// FP32 operands, so infinities act as in scalar arithmetic).  A workgroup takes
+// 64 samples at a time, 16 per wavefront: the forward tile and the
+// back-propagated sums D1^T = W2^T D2^T in index order.  The weight gradients
+// gW2 = D2 H1^T and gW1 = D1 X^T are products with the 64 samples as the
+// contraction, wavefront w taking the rows 16 w ..: there a lane needs several
+// samples of one hidden unit where the layers leave four units of one sample,
+// so D2, H1, D1, X (and E = dz relu(a2), whose row sums are gW3) pass through
+// LDS (rows of GROW values: 16-byte aligned for four-sample loads, successive
+// rows four banks apart).  The gradient stays in registers over all of a
+// workgroup's samples, which leaves one partial gradient.
 // Bound by latency at the usual batch (8192 samples are one pass of 128
 // workgroups), so the parameters come through LDS too: read by the lanes of
 // each operand straight from memory, two bytes at a time, they took most of
-// a 25 us kernel.  Loss, gradient and Adam step of a batch of 8192: 88 us
-// with vector arithmetic fed from LDS, 32 samples per workgroup (24 us), and
-// a reduction that walked its 256 partials one after the other on 21
-// workgroups (63 us); now 24 us, which the host needs to issue it (the kernel
-// 17 us, 16 at 300 samples, 38 at 60 000).  Relative error of the gradient
-// against 64 bits at 8192 samples as before, 3e-7.
+// a 25 us kernel.  Loss and gradient of 200, 8192, 60 000, 300 000 samples:
+// 16.3, 18.5, 38, 121 us.  The same products with both operands split in three
+// BF16 parts, six products each, took 16.9, 19.5, 41.5, 139: the splitting costs
+// more vector instructions than the FP32 matrix rate.  (Vector arithmetic fed
+// from LDS, 32 samples per workgroup, and a reduction that walked its partials
+// one after the other on 21 workgroups: 23, 85, 529, 2657.)  Relative error
+// of the gradient against 64 bits at 8192 samples 5e-8 (2.3e-7 with the serial
+// reduction).
 constexpr int GWAVES = 4;
 constexpr int GS = MX_TILE * GWAVES;   // samples per workgroup and pass
 constexpr int GROW = GS + 4;           // LDS row
 constexpr int GROWS = 4 * HID + NIN;   // D2, D1, E, H1, X
 constexpr int GBLOCKS = 256;           // most workgroups (one per CU)
 
-// eight samples (s0 ..) of LDS row r as the three BF16 parts of an operand
-__device__ __forceinline__ void grad_operand(const float *rows, int r, int s0, mx_b8 *o)
+// four samples (s0 ..) of LDS row r
+__device__ __forceinline__ mx_f4 grad_operand(const float *rows, int r, int s0)
 {
-    float v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = rows[r * GROW + s0 + i];
-    mx_s8 h, m, l;
-    split3v(v, 8, h, m, l);
-    o[0] = as_b8(h);
-    o[1] = as_b8(m);
-    o[2] = as_b8(l);
+    return *(const mx_f4 *)(rows + r * GROW + s0);
 }
 
 __global__ void __launch_bounds__(64 * GWAVES) k_mlp_grad(const uint16_t *theta, const float *x, const float *y, long n,
@@ -387,18 +370,12 @@ __global__ void __launch_bounds__(64 * GWAVES) k_mlp_grad(const uint16_t *theta,
         for (int i = 0; i < 4; ++i) W3[b][i] = bf2f(w.W3[16 * b + 4 * i + kq]);
     const float b3 = bf2f(w.b3[0]);
     // W2 transposed, in the same unit order: out 16 b + 4 (col % 4) + col / 4,
-    // summed over the units 4 i + kq of a block pair
-    mx_b8 A2T[4][2];
+    // summed over the units 4 t + kq
+    float A2T[4][16];
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            mx_s8 q;
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                q[i] = (short)w.W2[(16 * (2 * kb + (i >> 2)) + 4 * (i & 3) + kq) * HID + 16 * b + 4 * (col & 3) + (col >> 2)];
-            A2T[b][kb] = as_b8(q);
-        }
+        for (int t = 0; t < 16; ++t) A2T[b][t] = bf2f(w.W2[(4 * t + kq) * HID + 16 * b + 4 * (col & 3) + (col >> 2)]);
     __syncthreads();                     // the rows take the parameters' place
     float *D2 = pool, *D1 = D2 + HID * GROW, *EE = D1 + HID * GROW, *H1 = EE + HID * GROW, *X = H1 + HID * GROW;
     mx_f4 gW2[4], gW1 = {0.f, 0.f, 0.f, 0.f};
@@ -431,51 +408,46 @@ __global__ void __launch_bounds__(64 * GWAVES) k_mlp_grad(const uint16_t *theta,
             loss += (z > 0.f ? z + log1pf(expf(-z)) : log1pf(expf(z))) - yy * z;
             gb3 += dz;
         }
-        mx_s4 dh[4], dm[4], dl[4];
+        float d2[4][4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            float d2[4];
+        for (int c = 0; c < 4; ++c)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int row = 16 * c + 4 * i + kq;
-                d2[i] = a2[c][i] > 0.f ? dz * W3[c][i] : 0.f;
-                D2[row * GROW + sl] = d2[i];
+                d2[c][i] = a2[c][i] > 0.f ? dz * W3[c][i] : 0.f;
+                D2[row * GROW + sl] = d2[c][i];
                 EE[row * GROW + sl] = dz * (a2[c][i] > 0.f ? a2[c][i] : 0.f);
                 H1[row * GROW + sl] = a1[c][i] > 0.f ? a1[c][i] : 0.f;
             }
-            split3v(d2, 4, dh[c], dm[c], dl[c]);
-        }
-        mx_b8 kh[2], km[2], kl[2];
+        mx_f4 d1[4];
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            kh[kb] = join8(dh[2 * kb], dh[2 * kb + 1]);
-            km[kb] = join8(dm[2 * kb], dm[2 * kb + 1]);
-            kl[kb] = join8(dl[2 * kb], dl[2 * kb + 1]);
-        }
+        for (int b = 0; b < 4; ++b) d1[b] = mx_f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            mx_f4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < 16; ++t)
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) acc = mfma3k32(A2T[b][kb], kh[kb], km[kb], kl[kb], acc);
+            for (int b = 0; b < 4; ++b) d1[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(A2T[b][t], d2[t >> 2][t & 3], d1[b], 0, 0, 0);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) D1[(16 * b + 4 * i + kq) * GROW + sl] = a1[b][i] > 0.f ? acc[i] : 0.f;
-        }
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) D1[(16 * b + 4 * i + kq) * GROW + sl] = a1[b][i] > 0.f ? d1[b][i] : 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) X[(4 * i + kq) * GROW + sl] = xs[i];
         __syncthreads();
         // this wavefront's 16 rows of both weight gradients, and a row sum per lane
+        // (an operand slot of lane group kq carries sample ks + 4 kq + j in A and B alike)
 #pragma unroll
-        for (int ks = 0; ks < GS; ks += 32) {
-            mx_b8 a[3], o[3];
-            grad_operand(D2, 16 * wv + col, ks + 8 * kq, a);
+        for (int ks = 0; ks < GS; ks += 16) {
+            const mx_f4 a = grad_operand(D2, 16 * wv + col, ks + 4 * kq), e = grad_operand(D1, 16 * wv + col, ks + 4 * kq);
+            const mx_f4 xo = grad_operand(X, col, ks + 4 * kq);
+            mx_f4 h[4];
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                grad_operand(H1, 16 * b + col, ks + 8 * kq, o);
-                gW2[b] = mfma6k32(a, o, gW2[b]);
+            for (int b = 0; b < 4; ++b) h[b] = grad_operand(H1, 16 * b + col, ks + 4 * kq);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) gW2[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], h[b][j], gW2[b], 0, 0, 0);
+                gW1 = __builtin_amdgcn_mfma_f32_16x16x4f32(e[j], xo[j], gW1, 0, 0, 0);
             }
-            grad_operand(D1, 16 * wv + col, ks + 8 * kq, a);
-            grad_operand(X, col, ks + 8 * kq, o);
-            gW1 = mfma6k32(a, o, gW1);
         }
         if (wv < 3) {
             const float *row = pool + (wv * HID + lane) * GROW;
