@@ -202,7 +202,17 @@ __device__ __forceinline__ void rhs_lane(const Tables &t, const real *u, const C
             Phys::phys(d, ndn, fn, ctx);
             const real lam = dmax(so[d], Phys::speed(d, ndn, ctx));
 #pragma unroll
-            for (int v = 0; v < M; ++v) fnum[v] = real(0.5) * (fo[v] + fn[v]) - real(0.5) * lam * (uR[v] - uL[v]);
+            for (int v = 0; v < M; ++v) {
+                // both fluxes rounded before the sum: a product fused into it
+                // would be one side's here and the other's in the neighbour,
+                // and the face would have two fluxes
+                real sum;
+                {
+#pragma clang fp contract(off)
+                    sum = fo[v] + fn[v];
+                }
+                fnum[v] = real(0.5) * sum - real(0.5) * lam * (uR[v] - uL[v]);
+            }
         } else {
             real fL[M], fR[M];
             Phys::phys(d, aL, fL, ctx);
