@@ -31,6 +31,28 @@ struct RhsShape {
 template <typename real>
 constexpr bool rhs_ahead() { return sizeof(real) == 8; }
 
+// Surface flux of the state u with the fields nd, the same bits for the same
+// state and fields wherever it is formed.  Euler: from the momentum and energy
+// as they are, every operation rounded by itself (which products the compiler
+// fuses depends on what else the code around needs of them).  GLM-MHD: so for
+// the mass, a product; the scheme does not conserve the other totals.
+template <typename real, int EQ, int DIM, int FLUX>
+__device__ __forceinline__ void surface_flux(int d, const real *u, const real *nd, real *f, const Ctx<real> &ctx)
+{
+#pragma clang fp contract(off)
+    using Phys = typename PhysOf<real, EQ, DIM, FLUX>::type;
+    if constexpr (EQ == EQ_EULER) {
+        const real s = Phys::HALF ? real(2) : real(1);
+        const real vd = s * nd[1 + d], p = s * nd[Phys::P];
+        f[0] = u[1 + d];
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) f[1 + k] = (k == d) ? u[1 + k] * vd + p : u[1 + k] * vd;
+        f[DIM + 1] = (u[DIM + 1] + p) * vd;
+    } else {
+        Phys::phys(d, nd, f, ctx);
+    }
+}
+
 // Semi-discrete FR residual of one node (one lane): R = volume term of
 // Section 3 + the g2 surface corrections of eq:general.non.conservative.fr.one,
 // so that du/dt = -R.  The correction functions are Huynh's g2 on GLL
@@ -194,24 +216,25 @@ __device__ __forceinline__ void rhs_lane(const Tables &t, const real *u, const C
             uR[v] = side ? un[v] : uo[v];
         }
         real fnum[M], fo[M];
-        if constexpr (AHEAD) Phys::phys(d, nd, fo, ctx);
+        if constexpr (AHEAD) surface_flux<real, EQ, DIM, FLUX>(d, uo, nd, fo, ctx);
         if (surface == SURF_EC) {
             Phys::pair(d, aL, aR, fnum, ctx);
         } else if constexpr (AHEAD) {
             real fn[M];
-            Phys::phys(d, ndn, fn, ctx);
+            surface_flux<real, EQ, DIM, FLUX>(d, un, ndn, fn, ctx);
             const real lam = dmax(so[d], Phys::speed(d, ndn, ctx));
+            const real hs = side ? real(0.5) * lam : real(-0.5) * lam;
 #pragma unroll
             for (int v = 0; v < M; ++v) {
-                // both fluxes rounded before the sum: a product fused into it
-                // would be one side's here and the other's in the neighbour,
-                // and the face would have two fluxes
+                // both fluxes rounded before the sum, too: a product fused into
+                // it would be one side's here and the other's in the
+                // neighbour, and the face would have two fluxes
                 real sum;
                 {
 #pragma clang fp contract(off)
                     sum = fo[v] + fn[v];
                 }
-                fnum[v] = real(0.5) * sum - real(0.5) * lam * (uR[v] - uL[v]);
+                fnum[v] = real(0.5) * sum - hs * (un[v] - uo[v]);
             }
         } else {
             real fL[M], fR[M];
