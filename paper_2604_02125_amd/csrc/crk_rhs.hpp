@@ -23,13 +23,29 @@ struct RhsShape {
 
 // FP64 loads ahead of the volume term what the surface term and the stage
 // sums need, and forms each node's own surface flux once: 42 -> 31 us per
-// stage (Kelvin-Helmholtz 256^2, Kennedy-Gruber, degree 3; 665 -> 570 us for
+// stage (Kelvin-Helmholtz 256^2, Kennedy-Gruber, degree 3; 665 -> 560 us for
 // four RK4 steps with their dt), now 4.5 TB/s of the stage's 145 MB.  FP32
 // keeps the order of operations of its own: there the compiler contracts the
 // regrouped sums into other fused multiply-adds, and a run would round
 // otherwise than before.
 template <typename real>
 constexpr bool rhs_ahead() { return sizeof(real) == 8; }
+// A stage also holds u^n and the sum over the earlier stages, with the
+// neighbours' traces 36 doubles a lane in GLM-MHD: at degree 3, and at degree 2
+// with the central flux, they cost the second wavefront per SIMD.  There they
+// are loaded ahead only while a mesh has no second wavefront to lose
+// (AHEAD_WAVES).  us for two steps of n^2 elements, late / ahead: Derigs degree 3
+// (16 n^2 / 64 wavefronts) n = 32 98/80, 64 122/97, 72 146/160, 160 432/468;
+// central 3 95/81, 119/97, 137/158, 421/472; central 2 (2 per 14 elements) n =
+// 80 122/97, 90 131/156, 160 258/289.  Elsewhere ahead always (two steps of 256^2, late /
+// ahead: Derigs degree 1 335/261, 2 614/498, 4 4841/4800; central 1 314/250, 4 6193/4870;
+// Euler degree 3 337/286 Kennedy-Gruber, 405/335 Ranocha, 328/284 central).
+template <typename real, int EQ, int N, int FLUX>
+constexpr bool stage_ahead_always()
+{
+    return rhs_ahead<real>() && !(EQ == EQ_MHD && (N == 3 || (N == 2 && FLUX == VOL_CENTRAL)));
+}
+constexpr long AHEAD_WAVES = 1024;   // one per SIMD
 
 // Surface flux of the state u with the fields nd, the same bits for the same
 // state and fields wherever it is formed.  Euler: from the momentum and energy
@@ -63,7 +79,7 @@ __device__ __forceinline__ void surface_flux(int d, const real *u, const real *n
 // takes the mirrored symmetric fluxes from its line neighbours through LDS.
 // Every lane of the workgroup must call it; spare lanes (le set to 0 by the
 // caller) compute on element 0 and discard the result.
-template <typename real, int EQ, int DIM, int N, int FLUX, int BLK>
+template <typename real, int EQ, int DIM, int N, int FLUX, int BLK, bool AHEAD>
 __device__ __forceinline__ void rhs_lane(const Tables &t, const real *u, const Ctx<real> &ctx, int surface, int tid,
                                          int le, int node, long es, real *smem, real *R)
 {
@@ -75,7 +91,6 @@ __device__ __forceinline__ void rhs_lane(const Tables &t, const real *u, const C
     constexpr int NF = Phys::NF;
     constexpr bool SYM = Shape::SYM;
     constexpr int NPRIM = Shape::NPRIM, KSELF = Shape::KSELF;
-    constexpr bool AHEAD = rhs_ahead<real>();
     real *lds = smem;
     real *xch = smem + NF * BLK;
     const int base = le * NP;
@@ -85,7 +100,7 @@ __device__ __forceinline__ void rhs_lane(const Tables &t, const real *u, const C
     real uo[M], nd[NF];
 #pragma unroll
     for (int v = 0; v < M; ++v) uo[v] = u[((long)v * E + es) * NP + node];
-    // FP64: the neighbours' traces at the faces through this node are loaded by
+    // AHEAD: the neighbours' traces at the faces through this node are loaded by
     // every lane at once with its own state (an interior lane its own node
     // again, which it drops), so that no load waits behind the volume term
     real ut[DIM][M];
@@ -177,7 +192,7 @@ __device__ __forceinline__ void rhs_lane(const Tables &t, const real *u, const C
     // surface correction at the end nodes of each line:
     // s/(w dx_d) (F_num + F_num^nc - f(u_p) - B_d(u_p) g_d(u_p)), s = +1 at
     // xi_d = 1 and -1 at xi_d = 0
-    // FP64 also forms the node's own flux and wave speed once (every lane, so
+    // AHEAD also forms the node's own flux and wave speed once (every lane, so
     // that both directions share the square root)
     real so[DIM];
     if constexpr (AHEAD) {
@@ -281,7 +296,7 @@ k_fr_rhs(const Tables t, const void *u_, const double *dtc, int surface, void *r
     const long es = valid ? e : 0;
     const Ctx<real> ctx = make_ctx<real>(t, dtc);
     real R[M];
-    rhs_lane<real, EQ, DIM, N, FLUX, BLK>(t, (const real *)u_, ctx, surface, tid, le, node, es, smem, R);
+    rhs_lane<real, EQ, DIM, N, FLUX, BLK, rhs_ahead<real>()>(t, (const real *)u_, ctx, surface, tid, le, node, es, smem, R);
     if (!valid) return;
     real *rhs = (real *)rhs_;
 #pragma unroll
@@ -295,7 +310,7 @@ k_fr_rhs(const Tables t, const void *u_, const double *dtc, int surface, void *r
 // or, after the last stage, u^{n+1} = u^n + dt sum_m b_m K_m.  K_i is kept
 // (k[i]) where a later stage or the final sum needs it.  Sums run over m in
 // ascending order.
-template <typename real, int EQ, int DIM, int N, int FLUX>
+template <typename real, int EQ, int DIM, int N, int FLUX, bool AHEAD>
 __global__ void __launch_bounds__(tile_block<DIM == 2 ? (N + 1) * (N + 1) : N + 1>())
 k_rkfr_stage(const Tables t, const RkPtrs a, int i)
 {
@@ -313,7 +328,6 @@ k_rkfr_stage(const Tables t, const RkPtrs a, int i)
     if (le >= EPB) le = 0;
     const long es = valid ? e : 0;
     const Ctx<real> ctx = make_ctx<real>(t, a.dt);
-    constexpr bool AHEAD = rhs_ahead<real>();
     real u0[M], sum[M];
     if constexpr (AHEAD) {
         // u^n and the sum over the earlier stages, loaded with the stage's state
@@ -333,7 +347,7 @@ k_rkfr_stage(const Tables t, const RkPtrs a, int i)
         }
     }
     real R[M];
-    rhs_lane<real, EQ, DIM, N, FLUX, BLK>(t, (const real *)a.x_in, ctx, SURF_RUSANOV, tid, le, node, es, smem, R);
+    rhs_lane<real, EQ, DIM, N, FLUX, BLK, AHEAD>(t, (const real *)a.x_in, ctx, SURF_RUSANOV, tid, le, node, es, smem, R);
     if (!valid) return;
     const int S = t.stages;
     const real h = real(a.dt[0]);
@@ -372,11 +386,19 @@ hipError_t launch_rkfr(const Tables &t, const RkPtrs &p0, void *buf0, void *buf1
     constexpr int TB = tile_block<NP>();
     constexpr int EPB = TB / NP;
     const long grid = (t.nelem + EPB - 1) / EPB;
+    constexpr bool ALWAYS = stage_ahead_always<real, EQ, N, FLUX>();
+    const bool ahead = ALWAYS || (rhs_ahead<real>() && grid * (TB / 64) <= AHEAD_WAVES);
     RkPtrs p = p0;
     for (int i = 0; i < t.stages; ++i) {
         p.x_in = i == 0 ? p0.u_n : (i % 2 ? buf0 : buf1);
         p.x_out = i + 1 == t.stages ? u_out : (i % 2 ? buf1 : buf0);
-        hipLaunchKernelGGL((k_rkfr_stage<real, EQ, DIM, N, FLUX>), dim3((unsigned)grid), dim3(TB), 0, s, t, p, i);
+        if (ahead) {
+            if constexpr (rhs_ahead<real>())
+                hipLaunchKernelGGL((k_rkfr_stage<real, EQ, DIM, N, FLUX, true>), dim3((unsigned)grid), dim3(TB), 0, s, t, p, i);
+        } else {
+            if constexpr (!ALWAYS)
+                hipLaunchKernelGGL((k_rkfr_stage<real, EQ, DIM, N, FLUX, false>), dim3((unsigned)grid), dim3(TB), 0, s, t, p, i);
+        }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
