@@ -126,25 +126,32 @@ __device__ __forceinline__ void lnmean_parts_fast(real x, real y, real lx, real 
     den = series ? poly : (ly - lx);
 }
 
-// In FP64 no logarithm is needed unless two states differ by almost a factor
-// of two: with u = ((x - y)/(x + y))^2 <= 0.09 (a ratio up to 1.857) the
-// denominator 2 artanh(sqrt u)/sqrt u is its Chebyshev interpolant of degree 9
-// in u (relative error below 1e-17), more accurate than the difference of two
-// rounded logarithms.  Beyond it (and for a NaN or a state that is not
-// positive, whose logarithm must be NaN) the quotient's logarithm is formed,
-// in a branch that a wavefront takes only if one of its pairs needs it.
+// In FP64 the denominator needs no logarithm: with u = ((x - y)/(x + y))^2 <=
+// 0.09 (a ratio up to 1.857) 2 artanh(sqrt u)/sqrt u is its Chebyshev
+// interpolant of degree 9 in u (relative error below 1e-17), more accurate than
+// the difference of two rounded logarithms.  Farther states are scaled by a
+// power of two first (lnmean_scale), in a branch that a wavefront takes only if
+// one of its pairs needs it.  Relative error of a far mean's denominator against 80-bit
+// arithmetic: 2.6e-16 at most, 4.4e-17 rms (ln y - ln x: 1.6e-15 and 2.6e-16).
 // Per node and stage that saves two logarithms and two fields to exchange.
 // us per step, logarithms per node / this (FP64): Ranocha n^2, degree 3, no
 // limiter 128 38.1/35.5, 256 98/88, 400 223/194; degree 1 256 34.9/32.1;
-// density wave of 64 elements 4.35/3.57; GLM-MHD degree 4 192^2 346/322.
+// density wave of 64 elements 4.35/3.5; GLM-MHD degree 4 192^2 346/320.
+// Where every pair is far (random states that differ by up to e^4 from node to
+// node) Ranocha degree 3 256^2 113/125 and GLM-MHD degree 3 297/325 are slower,
+// degree 1 42/42, the others faster; with one such element in twenty all are
+// faster or the same (109/103, 297/278, 40/40).  The density wave on 4 to 32 elements, mostly
+// far, 100 steps: degree 3 519/478, degree 4 880/820.
 // Ranocha at degrees 2 and 4 keeps the logarithms: there (four pairs per node
-// at degree 4, three wavefronts per SIMD) the branches cost more than they
-// save (degree 4 256^2 235/257, with the limiter 253/304; degree 2 57/58),
+// at degree 4, three wavefronts per SIMD) the branch costs more than it
+// saves (degree 4 256^2 235/257, with the limiter 253/304; degree 2 57/58),
 // except in the batch's degree-4 tiles (512 problems 10.22/9.91 ms per two
 // steps).
-// Tried against the branches: every pair first, far ones formed once more in
-// a loop behind (16 to 18 registers more, a wavefront fewer); both means of a
-// far pair in one looped copy of the code (30 registers more).
+// The branch is uniform and out of the way, both means straight through it: against
+// the quotient's logarithm, one mean after the other in a divergent branch,
+// the density wave on 51 elements 347 -> 340 us, on 16 of degrees 3 and 4 568 -> 477 and
+// 1037 -> 824, all far at 256^2 as above 140 -> 125 and 370 -> 325.  Only the scaling in
+// the branch and the interpolant shared by all: the wave on 51 362, all far 116.
 constexpr double LNMEAN_UMAX = 0.09;
 __device__ __forceinline__ double lnmean_u(double x, double y)
 {
@@ -168,13 +175,24 @@ __device__ __forceinline__ double lnmean_den(double u)
     p = fma(p, u, 0x1.5555555555617p-1);
     return fma(p, u, 2.0);
 }
-// numerator and denominator of a mean of far states; the smaller state first,
-// so that both orders give the same bits
-__device__ __forceinline__ void lnmean_log(double x, double y, double &num, double &den)
+// Numerator and denominator of the mean of two far states a < b (the smaller
+// first, so that both orders give the same bits): b/a = 2^k b/c with c = 2^k a
+// within a factor of sqrt 2 of b, so ln(b/a) = k ln 2 + 2 artanh f,
+// f = (b - c)/(b + c), and the interpolant serves here too.  A quotient below 1
+// (a state that is not positive), or beyond all range, gives NaN.
+__device__ __forceinline__ void lnmean_far_parts(double x, double y, double &num, double &den)
 {
+    constexpr double LN2 = 0.69314718055994531, SQRT2 = 1.4142135623730951;
     const double a = fmin(x, y), b = fmax(x, y);
-    num = b - a;
-    den = log_fp64(a > 0.0 ? b * rcp_nr(a) : -1.0);
+    const double q = b * __builtin_amdgcn_rcp(a);
+    const int k = __builtin_amdgcn_frexp_exp(q * SQRT2) - 1;
+    const double c = __builtin_amdgcn_ldexp(a, k), s = b + c, d = b - c;
+    const double r = rcp_est1(s);
+    double f = d * r;
+    f = fma(fma(-s, f, d), r, f);
+    f = q >= 1.0 && q <= 1e300 ? f : __builtin_nan("");
+    num = fabs(y - x);                                   // (a NaN among the states: fmin and fmax drop it)
+    den = fma((double)k, LN2, f * lnmean_den(f * f));
 }
 // numerators and denominators of the two means of a pair, without logarithms
 // of the states
@@ -187,9 +205,14 @@ __device__ __forceinline__ void lnmean_parts2(double x1, double y1, double x2, d
     d1 = lnmean_den(u1);
     d2 = lnmean_den(u2);
     const bool far1 = lnmean_far(u1), far2 = lnmean_far(u2);
-    if (far1 || far2) {
-        if (far1) lnmean_log(x1, y1, n1, d1);
-        if (far2) lnmean_log(x2, y2, n2, d2);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(far1 || far2) != 0, 0)) {
+        double nf, df;
+        lnmean_far_parts(x1, y1, nf, df);
+        n1 = far1 ? nf : n1;
+        d1 = far1 ? df : d1;
+        lnmean_far_parts(x2, y2, nf, df);
+        n2 = far2 ? nf : n2;
+        d2 = far2 ? df : d2;
     }
 }
 
