@@ -715,7 +715,6 @@ crk_status crk_advance(crk_solver *s, const void *u_in, void *u_out, double *dt_
     if (instances) {
         StepPtrs p{};
         p.instances = instances;
-        p.learned = s->mlp != nullptr;
         p.u_in = u_in; p.u_out = u_out; p.dt = dt_dev; p.traces = tr;
         p.stage_tr = s->stagewise ? s->ws + s->off_stage : nullptr;
         p.alpha_raw = lim ? araw : nullptr;

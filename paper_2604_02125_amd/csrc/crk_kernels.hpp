@@ -184,7 +184,6 @@ struct StepPtrs {
     // blending code, bit 1 the one with it (0: both); either launches only
     // where the configuration uses it
     int instances;
-    int learned;   // local phase: the coefficients come from the learned indicator
     // MHD with the stage-wise non-conservative interface flux: the stage
     // states u^(j) at the face nodes, [face][j][v][e][k] (local phase
     // writes, interface phase reads); nullptr: the reduced form
@@ -1900,15 +1899,18 @@ constexpr long SPLIT_WAVES = 4 * 1024;
 //   FP32 64: 19.6/16.9 | 20.0/17.2; 256: 49.5/47.1 | 58.3/52.2 | 61/50;
 //        512: 132/130 | 170/161 | 160/149; 1000: 524/544 | 700/658 | 621/606
 // so two launches where a mesh has more than 16 wavefronts per SIMD in FP64
-// (256^2), 64 in FP32 (512^2) -- except with a learned indicator, which is
-// bound where tiles do blend (512^2 FP64 325/306, FP32 185/174).  Elsewhere
-// the instances differ by a wavefront at most: Ranocha 256^2 FP64 93.9/92.7 |
+// (256^2), 64 in FP32 (512^2), so that a flow that hardly blends does not pay
+// for one that does.  The same with a learned indicator, no tile blends | all:
+// FP64 512 262/275 | 342/327; 900 769/822 | 1028/992; FP32 900 484/503 | 718/677;
+// a Kelvin-Helmholtz flow of 512^2 from t = 0 to 2.4, up to 0.6 % of its elements
+// blending, 266-278/277-280, at t = 3 (1.1 %) 284/283.
+// Elsewhere the instances differ by a wavefront at most: Ranocha 256^2 FP64 93.9/92.7 |
 // 112/106, 1000^2 1341/1350 | 1566/1535; degree 4 400^2 FP64 392/384 |
 // 428/420; degree 1 1024^2 FP64 393/377: one launch.
 template <typename real, int N, int FLUX>
-inline bool one_local_launch(long waves, const StepPtrs &p)
+inline bool one_local_launch(long waves)
 {
-    if (FLUX != VOL_KG || N == 1 || N == 4 || p.learned) return true;
+    if (FLUX != VOL_KG || N == 1 || N == 4) return true;
     return waves <= 1024 * (sizeof(real) == 8 ? 16 : 64);
 }
 template <typename real, int N, int FLUX>
@@ -1960,7 +1962,7 @@ hipError_t launch_local_one(const Tables &t, const StepPtrs &p, hipStream_t s)
     const bool blend = p.alpha != nullptr || p.alpha_raw != nullptr;
     const int which = p.instances ? p.instances : 3;
     if constexpr (EQ == EQ_EULER && DIM == 2 && FLUX != VOL_CENTRAL) {
-        if (blend && p.tiles_in != nullptr && one_local_launch<real, N, FLUX>((long)grid * (TB / 64), p)) {
+        if (blend && p.tiles_in != nullptr && one_local_launch<real, N, FLUX>((long)grid * (TB / 64))) {
             // (issued separately, both kinds of tile belong to the first launch)
             if (!(which & 1)) return hipSuccess;
             const dim3 g((grid + WB - 1) / WB), b(TB * WB);
