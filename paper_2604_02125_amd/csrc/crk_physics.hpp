@@ -66,26 +66,30 @@ __device__ __forceinline__ float rcp_nr(float x)
 // Natural logarithm in FP64, for the per-node logarithms of the EC fluxes.
 // x = 2^k m with m in [sqrt(1/2), sqrt(2)), f = m - 1, s = f / (2 + f):
 //   ln m = 2 artanh s = f - f^2/2 + s (f^2/2 + s^2 p(s^2)),
-// p = (2 artanh(s)/s - 2)/s^2 by its Chebyshev interpolant of degree 6 on
-// s^2 <= (3 - sqrt 8)^2 (error 5e-18 of ln m at most), with the rounding
-// errors of f^2/2, f - f^2/2 and of adding k ln 2 carried along.  About 50
-// vector instructions where the library's log takes 95, which were 30 % of
-// the Ranocha kernels' instructions (density wave of 64 elements 4.9 -> 4.3
-// us per step, batch of 512 Ranocha problems -6 %).  Error on the same 4
-// million arguments per range against 80-bit arithmetic: 0.289 to 0.291 ulp
-// rms (the library's 0.289 to 0.294), at most 0.75 ulp (0.65); the largest
-// absolute error on [1/2, 2] is the same 5.8e-17.  Zero gives -inf, a
-// negative x NaN, +inf and NaN themselves, as there.
+// the arrangement of FreeBSD's msun and its ancestor fdlibm (K. C. Ng), with
+// Cody and Waite's two-part ln 2 (Software Manual for the Elementary
+// Functions, 1980); p = (2 artanh(s)/s - 2)/s^2 by its Chebyshev interpolant of degree 6 on
+// s^2 <= (3 - sqrt 8)^2 (error 5e-18 of ln m at most).  The rounding errors of
+// the denominator 2 + f, of f^2/2, of f - f^2/2, of adding k ln 2 and of adding
+// the small part are carried along, which takes every operation as written
+// (contracted, f^2/2's was taken off twice).  About 55
+// vector instructions where the library's log takes 95.  Error on the same 4
+// million arguments per range against 80-bit arithmetic, this / the library's:
+// [0.5, 2] 0.604/0.642 ulp at most and 0.2890/0.2934 rms, [0.9, 1.1] 0.506/0.636
+// and 0.2886/0.2963, [1e-12, 1e12] 0.572/0.630 and 0.0794/0.0798, between 0.7 and 0.72 or
+// 1.4 and 1.43, where it is largest, 0.618/0.616 and 0.2905/0.2972.
+// Zero gives -inf, a negative x NaN, +inf and NaN themselves, as there.
 __device__ __forceinline__ double log_fp64(double x)
 {
+#pragma clang fp contract(off)
     constexpr double ln2_hi = 0x1.62e42feep-1, ln2_lo = 0x1.a39ef358p-33;   // (ln2_hi: 31 bits, k ln2_hi exact)
     double m = __builtin_amdgcn_frexp_mant(x);           // [1/2, 1), also for denormals
     const bool low = m < 0.70710678118654752;
     const double k = (double)(__builtin_amdgcn_frexp_exp(x) - (low ? 1 : 0));
     m = __builtin_amdgcn_ldexp(m, low ? 1 : 0);
-    const double f = m - 1.0, g = 2.0 + f, r = rcp_est1(g);
+    const double f = m - 1.0, r = rcp_est1(2.0 + f);
     double s = f * r;
-    s = fma(fma(-g, s, f), r, s);
+    s = fma(fma(-f, s, fma(-2.0, s, f)), r, s);          // (f - 2 s is exact)
     const double z = s * s;
     double p = 0x1.2b584eb5559cbp-3;
     p = fma(p, z, 0x1.39fe6010f4be0p-3);
@@ -98,7 +102,8 @@ __device__ __forceinline__ double log_fp64(double x)
     const double h = f - hq, hl = ((f - h) - hq) - fma(hf, f, -hq);
     const double a = k * ln2_hi, S = a + h, Sl = (a - S) + h;
     const double t = fma(s, fma(z, p, hq), k * ln2_lo);
-    double y = S + (t + (hl + Sl));
+    const double Y = S + t, Yl = (S - Y) + t;
+    double y = Y + (Yl + (hl + Sl));
     if (__builtin_amdgcn_class(x, 0x27F))                // NaN, negative, zero, +inf
         y = x == 0.0 ? -INFINITY : (x < 0.0 ? __builtin_nan("") : x);
     return y;
