@@ -440,14 +440,15 @@ struct LocalShape {
     // coefficients 2 D_{p,q}/dx_d of the lane's rotations and diagonal come
     // from a table in LDS (one slot) instead of 2 (N+1) registers each, so
     // that one more wavefront per SIMD fits in registers and LDS (three at
-    // degree 4, four for Ranocha at degree 3).  Otherwise at degree 4 (MHD,
-    // bound at one wavefront by its registers; FP32, not register-bound) the
-    // node fields alternate between two sets of slots from stage to stage,
+    // degree 4, four for Ranocha at degree 3).  In FP32 at degree 4, where
+    // registers do not limit (Euler) or leave two wavefronts either way (MHD),
+    // the node fields alternate between two sets of slots from stage to stage,
     // so that a stage may overwrite them without waiting for the previous
-    // stage's readers (one barrier fewer per stage).
+    // stage's readers (one barrier fewer per stage).  (FP64 MHD at degree 4
+    // runs in crk_split.hpp.)
     static constexpr bool DTAB = DIM == 2 && EQ == EQ_EULER && sizeof(real) == 8 &&
                                  (N == 4 || (N == 3 && FLUX == VOL_RANOCHA));
-    static constexpr bool DBF = DIM == 2 && N == 4 && !DTAB;
+    static constexpr bool DBF = DIM == 2 && N == 4 && sizeof(real) == 4;
     static constexpr int DT = DTAB ? 1 : 0;
     static constexpr int slots = (DBF ? 2 : 1) * Phys::NL + NX + ASL + CS + XB + DT;
 };
