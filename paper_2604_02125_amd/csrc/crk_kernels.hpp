@@ -1880,6 +1880,11 @@ static __global__ void __launch_bounds__(DIAG_BLOCK) k_diag_final(int M, const d
 //   degree 3: 21/19 25/26 59/52 152/155 392/394: two up to four one-lane
 //     wavefronts per SIMD (192^2 is nine);
 //   degree 1 (no mirrored pairs to share): 24/30 at 96^2: one.
+// With the central flux the same or better (four steps of n^2, one / two lanes, n = 24,
+// 96, 192, 320): degree 2 88/88 142/140 325/307 768/729, degree 3 87/83 195/174 (one
+// from 192 on, by the rule), degree 4 115/107 360/368 1188/1167 3288/3291, although
+// its six-stage forms spill 14 and 22 registers at degrees 3 and 4 (dense six
+// stages: degree 3 at 96^2 239/209, degree 4 192^2 1184/1164).
 // FP32 has its second and third wavefront anyway (degree 4 176/179, degree 3
 // 71/81, degree 2 49/52 at 192^2).
 template <typename real, int N>
