@@ -737,7 +737,9 @@ crk_status crk_mlp_grad_workspace_bytes(int nin, int hidden, int64_t n, size_t *
     crk_status st = check_shape(nin, hidden);
     if (st) return st;
     if (!bytes || n < 0) { set_error(CRK_ERR_ARG, "bad argument"); return CRK_ERR_ARG; }
-    const long nb = (long)blocks(n, 32);   // (at least one partial gradient per workgroup)
+    // one set per 32 samples: the contract of this entry point and of the check
+    // below; the kernel uses one per 64 samples, 256 (5.4 MB) at most
+    const long nb = (long)blocks(n, 32);
     *bytes = ((size_t)nb * NPAR * sizeof(float) + 255) / 256 * 256 + (size_t)nb * sizeof(float);
     return CRK_OK;
 }
