@@ -41,7 +41,8 @@ PEAK_FP32_TFLOPS = 157.3
 # machine-readable "counters:" line per profiled workload and the digest of
 # the kernel sources it was taken with.  A figure is used only when that
 # digest matches the sources of this checkout; otherwise it is null.
-KERNEL_SOURCES = ("paper_2604_02125_amd/csrc/crk_kernels.hpp", "paper_2604_02125_amd/csrc/crk_physics.hpp")
+KERNEL_SOURCES = ("paper_2604_02125_amd/csrc/crk_kernels.hpp", "paper_2604_02125_amd/csrc/crk_physics.hpp",
+                  "paper_2604_02125_amd/csrc/crk_split.hpp")
 
 
 def profiled_counters(workload: str):
@@ -153,24 +154,25 @@ class Pipelined:
         self.n = 0
         crk._check(crk.lib().crk_prepare(self.s._h, crk._ptr(self.buf[0]), crk._ptr(self.dt), self.sp), "prepare")
 
-    def step(self, events=None):
-        """One pipelined step; with events (four torch.cuda.Event), record
-        them around the local phase's two launches and the interface phase."""
+    def step(self, marks=None):
+        """One pipelined step.  marks: torch.cuda.Events recorded on the way,
+        three around the local and the interface phase, or five around the
+        local phase's two halves, nothing, and the interface phase."""
         crk, L = self.crk, self.crk.lib()
         ui, uo = self.buf[self.n % 2], self.buf[(self.n + 1) % 2]
         p = crk._ptr
         h, a, b, d = self.s._h, p(ui), p(uo), p(self.dt)
-        if events is None:
-            crk._check(L.crk_advance(h, a, b, d, crk.PHASE_LOCAL, self.sp), "advance/local")
-            crk._check(L.crk_advance(h, a, b, d, crk.PHASE_INTERFACE, self.sp), "advance/iface")
+        if marks is not None and len(marks) == 5:
+            phases = (crk.PHASE_LOCAL_PLAIN, crk.PHASE_LOCAL_BLEND, None, crk.PHASE_INTERFACE)
         else:
-            events[0].record(self.stream)
-            crk._check(L.crk_advance(h, a, b, d, crk.PHASE_LOCAL_PLAIN, self.sp), "advance/local plain")
-            events[1].record(self.stream)
-            crk._check(L.crk_advance(h, a, b, d, crk.PHASE_LOCAL_BLEND, self.sp), "advance/local blend")
-            events[2].record(self.stream)
-            crk._check(L.crk_advance(h, a, b, d, crk.PHASE_INTERFACE, self.sp), "advance/iface")
-            events[3].record(self.stream)
+            phases = (crk.PHASE_LOCAL, crk.PHASE_INTERFACE)
+        for k, ph in enumerate(phases):
+            if marks is not None:
+                marks[k].record(self.stream)
+            if ph is not None:
+                crk._check(L.crk_advance(h, a, b, d, ph, self.sp), "advance")
+        if marks is not None:
+            marks[-1].record(self.stream)
         self.n += 1
 
     @property
@@ -180,12 +182,15 @@ class Pipelined:
 
 def timed(pipe, steps, warmup, events=False, settle=0.3):
     """Wall time of `steps` pipelined steps (no events inside).  With events,
-    the same steps are then run again from the initial state with HIP events
-    on the launch stream between the launches of every step, which gives the
-    average duration of the local phase's instance without the blending code
-    (the dominant kernel: every tile of a state where no coefficient is
-    positive), of the instance with it, and of the interface phase (its
-    kernel and the dt slots kernel), in milliseconds."""
+    the same steps are then run twice more from the initial state with HIP
+    events on the launch stream, in milliseconds: once around the local and the
+    interface phase (its kernel and the dt slots kernel), once around the two
+    halves of the local phase, the code without blending (every tile of a state
+    where no coefficient is positive) and the code with it.  Where one launch
+    serves both kinds of tile, or no limiter runs, the second half issues
+    nothing: its interval is then no longer than an interval without a call
+    (empty_interval_ms) and is given as None.  Every interval includes an
+    event's own few microseconds."""
     import torch
     # settle: keep the GPU busy with the same steps for a few tenths of a
     # second first, so that the timed steps see the clocks of a running
@@ -207,17 +212,23 @@ def timed(pipe, steps, warmup, events=False, settle=0.3):
     if not events:
         return el, None
     n = pipe.n
-    pipe.reset()
-    for _ in range(warmup):
-        pipe.step()
-    ev = [[torch.cuda.Event(enable_timing=True) for _ in range(4)] for _ in range(steps)]
-    for k in range(steps):
-        pipe.step(ev[k])
-    torch.cuda.synchronize()
-    assert pipe.n == n
-    mean = lambda i, j: sum(e[i].elapsed_time(e[j]) for e in ev) / steps
-    return el, {"k_local_plain_ms": mean(0, 1), "k_local_blend_ms": mean(1, 2), "interface_ms": mean(2, 3),
-                "local_phase_ms": mean(0, 2)}
+
+    def intervals(count):
+        pipe.reset()
+        for _ in range(warmup):
+            pipe.step()
+        ev = [[torch.cuda.Event(enable_timing=True) for _ in range(count + 1)] for _ in range(steps)]
+        for e in ev:
+            pipe.step(e)
+        torch.cuda.synchronize()
+        assert pipe.n == n
+        return [sum(e[i].elapsed_time(e[i + 1]) for e in ev) / steps for i in range(count)]
+
+    local, interface = intervals(2)
+    plain, blend, empty, _ = intervals(4)
+    issued = lambda t: t if t > 1.5 * empty else None
+    return el, {"k_local_plain_ms": issued(plain), "k_local_blend_ms": issued(blend), "empty_interval_ms": empty,
+                "interface_ms": interface, "local_phase_ms": local}
 
 
 def check_admissible(solver, u, what):
@@ -263,30 +274,38 @@ def gpu_steps(solver, u0, nsteps):
 
 def kernel_report(workload, kt, ndof, M, dim, N, stages, flux, precision, ms_step):
     """Roofline figures of a single-mesh workload from the live kernel times
-    kt (timed()): the dominant kernel is the local phase's instance without
-    the blending code.  Bytes and FLOPs are algorithmic (per DOF x DOFs per
-    launch) over that kernel's average duration; counter figures come from
-    the profile summary taken with the same kernel sources (else null)."""
+    kt (timed()): the dominant kernel is the local phase's.  Bytes and FLOPs
+    are algorithmic (per DOF x DOFs per launch) over that kernel's average
+    duration; counter figures, and the kernel's name, come from the profile
+    summary taken with the same kernel sources (else null, and no name)."""
     elem = 8 if precision == "fp64" else 4
-    # the instance that did the work: without tile flags (Ranocha, or no
-    # limiter) one of the two launches is empty
-    plain = kt["k_local_plain_ms"] >= kt["k_local_blend_ms"]
-    t_ms = kt["k_local_plain_ms"] if plain else kt["k_local_blend_ms"]
+    # the launch that did the work: the only one, or the longer of the two
+    both = {k: kt[k] for k in ("k_local_plain_ms", "k_local_blend_ms") if kt[k] is not None}
+    both = both or {"k_local_plain_ms": kt["local_phase_ms"]}
+    plain = max(both, key=both.get) == "k_local_plain_ms"
+    t_ms = max(both.values())
     t = t_ms * 1e-3
+    rec = profiled_counters(workload)
+    if rec is not None and rec.get("kernel_instance") != ("plain" if plain else "blend"):
+        rec = None
+    name = "local stages, the launch " + ("of every tile" if len(both) == 1 else
+                                          "of the tiles that " + ("cannot blend" if plain else "can blend"))
+    if rec is not None:
+        name += f": {rec['kernel']}"
     kb = k2_bytes_per_dof(M, dim, N, elem) * ndof
     db = k2_design_bytes_per_dof(M, dim, N, elem) * ndof
     sb = step_bytes_per_dof(M, dim, N, elem) * ndof
     ff = k2_formula_flops_per_dof(flux, N, dim, stages, M) * ndof
     peak_f = PEAK_FP64_TFLOPS if precision == "fp64" else PEAK_FP32_TFLOPS
     r = {"bound": "hbm",
-         "kernel": "k_local (local stages, instance " + ("without" if plain else "with") + " the blending code)",
+         "kernel": name,
          "achieved": kb / t / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": kb / t / 1e9 / PEAK_HBM_GBS,
          "traffic": None, "kernel_ms": t_ms,
          "algorithmic_bytes_per_dof": kb / ndof, "algorithmic_bytes_per_launch": kb,
          # this library's own traces (flux shares instead of U, F and u^n)
          "design_bytes_per_dof": db / ndof, "design_frac": db / t / 1e9 / PEAK_HBM_GBS,
          "local_phase_ms": kt["local_phase_ms"],
-         "other_instance_ms": kt["k_local_blend_ms"] if plain else kt["k_local_plain_ms"],
+         "other_launch_ms": min(both.values()) if len(both) == 2 else None,
          "interface_ms": kt["interface_ms"],
          # the whole step against its own algorithmic bytes
          "step_bytes_per_dof": sb / ndof, "step_achieved_gbs": sb / (ms_step * 1e-3) / 1e9,
@@ -294,9 +313,6 @@ def kernel_report(workload, kt, ndof, M, dim, N, stages, flux, precision, ms_ste
          "formula_flops_per_dof": ff / ndof, "formula_tflops": ff / t / 1e12, "vector_peak_tflops": peak_f,
          "formula_frac": ff / t / 1e12 / peak_f,
          "counter_tflops": None, "counter_frac": None, "counter_profile": None}
-    rec = profiled_counters(workload)
-    if rec is not None and rec.get("kernel_instance") != ("plain" if plain else "blend"):
-        rec = None
     if rec is not None:
         r["traffic"] = rec["hbm_bytes"]
         fl = rec.get("fp64_flops" if precision == "fp64" else "fp32_flops")
