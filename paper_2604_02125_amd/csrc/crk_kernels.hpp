@@ -1002,7 +1002,7 @@ k_local(const Tables t, const StepPtrs a)
 // at the blending instance's register count.  Same tile code, same bits.
 // Ranocha at degree 3 with classical RK4 is held to 128 registers, four
 // wavefronts per SIMD, without spills (130 and three else): local phase of
-// KHI 256^2 60 -> 57 us.  Other tableaus would spill (12 to 109), and
+// KHI 256^2 60 -> 57 us (55 now).  Other tableaus would spill (12 to 109), and
 // Kennedy-Gruber holds 156.
 template <typename real, int DIM, int N, int FLUX, int S, int TAB, int WPB>
 __global__ void __launch_bounds__(tile_block<DIM == 2 ? (N + 1) * (N + 1) : N + 1>() * WPB)

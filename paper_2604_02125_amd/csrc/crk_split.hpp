@@ -21,7 +21,8 @@
 // phase 345 -> 300 us (372 -> 346 us per step against the one-lane kernel
 // with the same pair flux and logarithm), bound by vector issue (62 % busy)
 // and LDS (53 %) together, the rest waiting at barriers.  With the series for
-// the logarithmic means the phase takes 262 to 288 us, the step 312.
+// the logarithmic means the phase took 262 us, the step 301; with far means in
+// one uniform branch 253 and 292.
 #pragma once
 #include "crk_kernels.hpp"
 
